@@ -48,7 +48,8 @@ typedef struct pctree_debug_config {
                                 would serve                                      */
   int32_t round_slices;      /* > 0: at most this many vocabulary slices in the
                                 single-launch round (default 0: one per compute
-                                unit but one, at most 256)                       */
+                                unit that its mergers and keepers leave, at most
+                                256)                                             */
   int32_t wide_unbounded;    /* nonzero: stages with more than 16 frontier rows
                                 ignore each row's lower bound of its k'-th best
                                 logit, so every logit is a candidate and every
@@ -68,13 +69,13 @@ pctree_status pctree_debug_set(const pctree_debug_config* cfg);
  * to the whole device).  Each stamp is one global store; the tree is the
  * same as the default build's.  The default library (libpctree.so) has no
  * stamps.  Rows of the array (who), stage d:
- *   0  keeper of the single-launch round: 0 merge starts, 1 every slice
- *      record seen and the rows merged, 2 stage selected (frontier
- *      published); stage PCTREE_TIMELINE_STAGES - 1: 0 stages done,
- *      1 emission done
+ *   0  request 0's keeper in the single-launch round: 0 its wait for the
+ *      stage's children words starts, 1 all of them seen, 2 stage selected
+ *      (pool and running top-N); stage PCTREE_TIMELINE_STAGES - 1: 0 stages
+ *      done, 1 emission done
  *   1  first streaming workgroup of the single-launch round, 2 the last
- *      one: 0 frontier wait begins, 1 head input built, 2 stream done,
- *      3 slice records published
+ *      one: 0 frontier wait begins, 1 head input built, 2 logits in LDS,
+ *      3 slice records and lists published
  *   3  per-stage launches, a stage of the wide form (every stage of a round
  *      whose frontier can exceed 16 rows): workgroup 0 of the head kernel:
  *      0 start, 1 stream done, 2 end

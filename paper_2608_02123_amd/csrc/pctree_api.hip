@@ -210,6 +210,7 @@ void plan_shape(Plan& p, int V, int B, int N, int k, int r, int R, int dtype) {
   p.N = N;
   p.k = k;
   p.kk = std::min(k, V);
+  p.kk_inv = 65536 / p.kk + 1;
   p.r = r;
   p.R = R;
   p.dtype = dtype;
@@ -249,7 +250,7 @@ size_t carve_workspace(Plan& p, char* base) {
   p.part_key = (uint64_t*)take(parts * p.kmax * sizeof(uint64_t));
   p.part_hd = (uint64_t*)take(parts * kRecWords * sizeof(uint64_t));
   p.req_bad = (int*)take(R * sizeof(int));
-  p.front_w = (uint64_t*)take((size_t)p.stages * p.rows_max * sizeof(uint64_t));
+  p.done_w = (uint64_t*)take((size_t)p.stages * p.rows_max * sizeof(uint64_t));
   p.tau = (float*)take((size_t)p.rows_max * sizeof(float));
   p.probe_tok = (int*)take(R * (size_t)p.B * kProbe * sizeof(int));
   p.probe_w = take(R * (size_t)p.B * kProbe * p.r * es);

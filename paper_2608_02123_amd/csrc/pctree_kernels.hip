@@ -6,20 +6,20 @@
 // scores (Eq. 4) and prunes the layer to k frontier nodes (Sec. 4.1); after B
 // stages the global top-N is emitted (Sec. 4.2, App. A).
 //
-// Every stage streams the whole head matrix W (V x r) once.  The V axis is cut
-// into slices; a workgroup streams its slice through bf16/f32 MFMA with the
-// parents as the 16 MFMA columns, folds each row into an online logsumexp and
-// a per-lane top-k list, and publishes one (max, sum, top-k) partial per row:
-// the V-wide child logits never leave the chip.  The partials of all slices
-// are then merged and the stage's selection runs.
+// Every stage needs the whole head matrix W (V x r).  The V axis is cut into
+// slices; a workgroup takes its slice through bf16/f32 MFMA with the parents
+// as the MFMA columns, and of each row leaves only its slice's (max, sum of
+// exp) and its few best tokens: the V-wide child logits never leave the chip.
+// The slices' partials are then merged per row and the stage's selection runs.
 //
 // Two launch forms:
 //  * narrow (R * k' <= 16 frontier rows, one MFMA column block): ONE persistent
-//    cooperative kernel per round.  After each stage the last workgroup to
-//    arrive merges the slices, selects, writes the next frontier's head input
-//    and releases the others; the last stage's selector also emits the tree.
+//    kernel per round.  W stays on chip (registers and LDS) for all B stages;
+//    merger workgroups settle the rows, every streaming workgroup ranks the
+//    next frontier from the mergers' words, and a keeper workgroup per request
+//    keeps and emits its tree.
 //  * wide (more rows): per stage a head launch over (slice, column block) and a
-//    per-request select launch; then an emit launch.
+//    per-request merge-and-select launch; then an emit launch.
 //
 // Ordering keys are unique 64-bit integers, so every selection is exact and
 // deterministic:
@@ -30,6 +30,7 @@
 #include "pctree.h"
 #include "pctree_plan.h"
 
+#include <float.h>
 #include <math.h>
 
 #include <algorithm>
@@ -78,18 +79,6 @@ constexpr float kLog2e = 1.4426950408889634f;
 __device__ __forceinline__ float exp2_raw(float x) { return __builtin_amdgcn_exp2f(x); }
 constexpr float kNegBig = -3.0e38f;  // "no value yet" for running maxima
 
-// A pointer known to address global memory.  Code that is not inlined into
-// a kernel cannot tell where the plan's pointers point and would use flat
-// accesses, which also count as LDS accesses for the waits on those.
-template <typename T>
-__device__ __forceinline__ const __attribute__((address_space(1))) T* gmem(const T* ptr) {
-  return (const __attribute__((address_space(1))) T*)ptr;
-}
-
-__device__ __forceinline__ void __atomic_thread_fence_agent_acquire() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-}
-
 __device__ __forceinline__ uint32_t f32_ord(float f) {
   uint32_t b = __float_as_uint(f);
   if (b == 0x80000000u) b = 0u;
@@ -128,6 +117,34 @@ __device__ __forceinline__ float silu_f32(float e, float h) {
   return (float)y;
 }
 
+// The same with exp(-x) by Cody and Waite's range reduction (-x = n ln 2 + r,
+// ln 2 split in two) and the Taylor series of e^r to r^13 (|r| <= ln 2 / 2: the
+// rest is below 2^-57), its constants read from `tab` in LDS: as literals they
+// would sit in registers over the whole stage loop of the persistent kernel.
+constexpr int kSiluTab = 17;
+__device__ __forceinline__ void silu_tab_init(double* tab) {
+  if (threadIdx.x == 0) {
+    tab[0] = 1.4426950408889634;       // log2 e
+    tab[1] = -0.693147182464599609375;    // -ln 2: to 24 bits (exact times n),
+    tab[2] = 1.904654299957767878542e-09;  // and the rest
+    double f = 1.0;
+    for (int k = 0; k < 14; ++k) {  // 1 / k!
+      tab[3 + k] = 1.0 / f;
+      f *= k + 1;
+    }
+  }
+}
+__device__ __forceinline__ float silu_f32_tab(float e, float h, const double* tab) {
+  const double x = (double)e + (double)h;
+  const double a = fmin(fmax(-x, -800.0), 800.0);  // (e^a is then 0 or infinite at the ends)
+  const double n = rint(a * tab[0]);
+  const double r = fma(n, tab[2], fma(n, tab[1], a));
+  double q = tab[16];
+#pragma unroll
+  for (int k = 12; k >= 0; --k) q = fma(q, r, tab[3 + k]);
+  return (float)(x / (1.0 + ldexp(q, (int)n)));
+}
+
 __device__ __forceinline__ uint16_t bf16_rne(float f) {
   uint32_t b = __float_as_uint(f);
   b += 0x7fffu + ((b >> 16) & 1u);
@@ -135,34 +152,27 @@ __device__ __forceinline__ uint16_t bf16_rne(float f) {
 }
 
 // The same bf16 head input, bf16(f32(SiLU(e + h) in float64)), mostly from
-// an f32 evaluation: x = e + h with its exact rounding error (two-sum),
-// exp(-x) by Cody and Waite's additive range reduction (x - n ln 2 with ln 2
-// split into a short high part, exact in the product, and a low part) and
-// the hardware 2^x on the reduced argument, the quotient
-// x / (1 + exp(-x)) refined by one Newton step, and a first-order correction
-// for the rounding of x.  The result lies within 6 bit steps of
-// f32(SiLU64(x)) by the error analysis (at most 3 seen over 10^9 draws with
-// |x| from 1e-3 to 30), so it rounds to the same bf16 unless it lies within
-// kSiluTol steps of a bf16 rounding midpoint.  Those elements (about 1 in
-// 4000), |x| >= 16, and zero or subnormal results take the float64 path.
-constexpr int kSiluTol = 8;
-__device__ __forceinline__ uint16_t silu_bf16(float e, float h) {
+// the plain f32 evaluation y = x / (1 + 2^(-x log2 e)) on the transcendental
+// unit.  In steps of y's last place it is off by at most (1 + |x|) for the
+// rounding of x = e + h (SiLU's elasticity), 1.3 |x| for the rounded exponent
+// and log2 e, and 6 for the hardware 2^x, the sum, the reciprocal and the
+// product: below 8 + 3 |x|.  So it rounds to the same bf16 unless it lies
+// within that of a bf16 rounding midpoint; those elements (about 1 in 3000 at
+// |x| ~ 1), |x| >= 16, and zero or subnormal results take the float64 path.
+// (A refined evaluation good to 6 steps took twice the instructions and left 1
+// element in 4000.)
+__device__ __forceinline__ float silu_fast(float e, float h, bool& ok) {
   const float x = e + h;
-  const float bb = x - e;
-  const float xe = (e - (x - bb)) + (h - bb);  // x + xe == e + h exactly
-  const float n = rintf(-x * kLog2e);
-  float r = fmaf(n, -0.693145751953125f, -x);  // ln 2 split: 0x3f317200 + 0x35bfbe8e
-  r = fmaf(n, -1.428606820309417232e-06f, r);
-  const float t = __builtin_amdgcn_ldexpf(exp2_raw(r * kLog2e), (int)n);  // exp(-x)
-  const float d = 1.0f + t;
-  float q = __builtin_amdgcn_rcpf(d);
-  q = fmaf(q, fmaf(-d, q, 1.0f), q);
-  float y = x * q;
-  y = fmaf(fmaf(-y, d, x), q, y);
-  y = fmaf(q * fmaf(x * t, q, 1.0f), xe, y);  // + SiLU'(x) * xe
+  const float y = x * __builtin_amdgcn_rcpf(1.0f + exp2_raw(x * -kLog2e));
   const uint32_t b = __float_as_uint(y);
-  const int lo = (int)(b & 0xffffu) - 0x8000;
-  const bool ok = fabsf(x) < 16.0f && (lo > kSiluTol || lo < -kSiluTol) && (b & 0x7f800000u) != 0u;
+  const int off = (int)(b & 0xffffu) - 0x8000;
+  ok = fabsf(x) < 16.0f && fabsf((float)off) > fmaf(fabsf(x), 3.0f, 8.0f) &&
+       (b & 0x7f800000u) != 0u;
+  return y;
+}
+__device__ __forceinline__ uint16_t silu_bf16(float e, float h) {
+  bool ok;
+  const float y = silu_fast(e, h, ok);
   return bf16_rne(ok ? y : silu_f32(e, h));
 }
 
@@ -303,13 +313,6 @@ __device__ __forceinline__ uint32_t dpp(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
 }
 
-template <int CTRL, int ROWS>
-__device__ __forceinline__ uint64_t dpp64(uint64_t v) {
-  return ((uint64_t)dpp<CTRL, ROWS>((uint32_t)(v >> 32)) << 32) | dpp<CTRL, ROWS>((uint32_t)v);
-}
-
-__device__ __forceinline__ uint64_t max_u64(uint64_t a, uint64_t b) { return a > b ? a : b; }
-
 __device__ __forceinline__ uint64_t readlane_u64(uint64_t v, int lane) {
   const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)v, lane);
   const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), lane);
@@ -370,6 +373,49 @@ __device__ __forceinline__ float wave_sum_f32(float v) {
   return __uint_as_float(__builtin_amdgcn_readlane((int)__float_as_uint(v), 63));
 }
 
+// A lane permutation in which every lane has a source (quad permutes, mirrors
+// and the like): folds into the instruction that uses it.
+template <int CTRL>
+__device__ __forceinline__ uint32_t perm(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
+}
+template <int CTRL>
+__device__ __forceinline__ float permf(float v) {
+  return __uint_as_float(perm<CTRL>(__float_as_uint(v)));
+}
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E;           // quad permutes
+constexpr int kHalfMirror = 0x141, kMirror = 0x140;  // within 8 and 16 lanes
+
+// Combine with lanes ^ 16 and ^ 32 (symmetric op on {own, partner}).
+template <int X, class Op>
+__device__ __forceinline__ uint32_t swap_op(uint32_t v, Op op) {
+  uint32_t a, b;
+  swap_pair<X>(v, a, b);
+  return op(a, b);
+}
+
+// Maximum over the wave, in every lane; values equal within each 2^S lanes.
+template <int S>
+__device__ __forceinline__ uint32_t all_max(uint32_t v) {
+  if (S < 1) v = max(v, perm<kXor1>(v));
+  if (S < 2) v = max(v, perm<kXor2>(v));
+  if (S < 3) v = max(v, perm<kHalfMirror>(v));
+  if (S < 4) v = max(v, perm<kMirror>(v));
+  auto mx = [](uint32_t a, uint32_t b) { return max(a, b); };
+  v = swap_op<16>(v, mx);
+  return swap_op<32>(v, mx);
+}
+__device__ __forceinline__ float all_sum(float v) {
+  v += permf<kXor1>(v);
+  v += permf<kXor2>(v);
+  v += permf<kHalfMirror>(v);
+  v += permf<kMirror>(v);
+  auto add = [](uint32_t a, uint32_t b) {
+    return __float_as_uint(__uint_as_float(a) + __uint_as_float(b));
+  };
+  return __uint_as_float(swap_op<32>(swap_op<16>(__float_as_uint(v), add), add));
+}
+
 // (m, s) pairs describe sum_i exp(z_i) = exp(m) * s; combine two of them.
 __device__ __forceinline__ void lse_combine(float& m, float& s, float om, float os) {
   const float nm = fmaxf(m, om);
@@ -421,7 +467,7 @@ __device__ __forceinline__ f32x4 mfma_chunk<0>(u32x4 a, u32x4 b, f32x4 acc) {
 // (token 0 stands in for an invalid root, whose tree is emitted empty), a
 // count of -1 that stays if the round is aborted, the trace's stage-0 row.
 // Threads [tid0, tid0 + nth) of the calling workgroup share the work.
-__device__ __forceinline__ void init_request_body(const Plan& p, int req, int tid, int nth) {
+__device__ __forceinline__ void init_request(const Plan& p, int req, int tid, int nth) {
   int root = p.root[req];
   const bool bad = root < 0 || root >= p.V;
   if (bad) root = 0;
@@ -444,10 +490,6 @@ __device__ __forceinline__ void init_request_body(const Plan& p, int req, int ti
       p.t_score[o] = first ? 0.0f : -INFINITY;
     }
   }
-}
-
-__device__ void init_request(const Plan& p, int req, int tid, int nth) {
-  init_request_body(p, req, tid, nth);
 }
 
 // Head rows per request of stage d, and whether stage d of a per-stage-launch
@@ -498,19 +540,13 @@ __device__ __forceinline__ float raw_to_f32(uint32_t r) {
 }
 
 // Lane geometry of a head pass over one block of 16 frontier rows.
-// With `fold` (at most 8 frontier rows) the C fragments of two tiles share
-// the 16 columns: columns 0..7 keep the first tile's rows, columns 8..15 take
-// the second tile's (moved up by 8), so that every lane holds a live row.  B
-// columns (the frontier rows fed to the MFMA) are unaffected.
 struct HeadLane {
   int lane, wave, col, grp;
   int row, req, slot;  // the frontier row whose logits this lane holds
   bool row_ok;
-  int half;            // which tile of a folded pair (0 without fold)
-  bool lead;           // the lane that publishes its row (first of a folded pair)
   int b_req, b_slot;   // the frontier row of this lane's B column
   bool b_ok;
-  __device__ HeadLane(const Plan& p, int P, int cb, bool fold = false) {
+  __device__ HeadLane(const Plan& p, int P, int cb) {
     lane = threadIdx.x & 63;
     wave = threadIdx.x >> 6;
     col = lane & 15;
@@ -520,12 +556,10 @@ struct HeadLane {
     b_ok = bcol < nrows;
     b_req = b_ok ? bcol / P : 0;
     b_slot = b_ok ? bcol - b_req * P : 0;
-    row = cb * kTile + (fold ? (col & 7) : col);
+    row = cb * kTile + col;
     row_ok = row < nrows;
     req = row_ok ? row / P : 0;
     slot = row_ok ? row - req * P : 0;
-    half = fold ? (col >> 3) : 0;
-    lead = !fold || col < 8;
   }
 };
 
@@ -660,50 +694,6 @@ __device__ __forceinline__ void tile_step(const Plan& p, const HeadLane& h,
   tile_epilogue<DT, KMAX>(p, h, acc, l, t, h.row_ok, r);
 }
 
-
-// Two tiles on two independent MFMA chains; the second tile's C fragment is
-// moved into columns 8..15 (DPP row_shr:8 onto banks 2-3 of every row), then
-// one epilogue covers both.  t is the lane's own tile (ta or tb by half).
-template <int DT, int NCMAX, int KMAX>
-__device__ __forceinline__ void tile_pair_step(const Plan& p, const HeadLane& h,
-                                               const u32x4 (&a0)[NCMAX], const u32x4 (&a1)[NCMAX],
-                                               const u32x4 (&b)[NCMAX], const uint32_t (&l)[4],
-                                               int t, bool ok, RowAcc<KMAX>& r) {
-  f32x4 c0 = {0.f, 0.f, 0.f, 0.f}, c1 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int c = 0; c < NCMAX; ++c) {
-    c0 = mfma_chunk<DT>(a0[c], b[c], c0);
-    c1 = mfma_chunk<DT>(a1[c], b[c], c1);
-  }
-  f32x4 acc;
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-    acc[i] = __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(c0[i]), __float_as_int(c1[i]),
-                                                        0x118, 0xF, 0xC, false));
-  tile_epilogue<DT, KMAX>(p, h, acc, l, t, ok && h.row_ok, r);
-}
-
-// tile_pair_step on two LDS-resident tiles (fragment order), reading each
-// rank chunk right before its MFMA so that only two chunks are live.
-template <int DT, int NCMAX, int KMAX>
-__device__ __forceinline__ void lds_pair_step(const Plan& p, const HeadLane& h, const u32x4* w0,
-                                              const u32x4* w1, const u32x4 (&b)[NCMAX],
-                                              const uint32_t (&l)[4], int t, bool ok,
-                                              RowAcc<KMAX>& r) {
-  f32x4 c0 = {0.f, 0.f, 0.f, 0.f}, c1 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int c = 0; c < NCMAX; ++c) {
-    c0 = mfma_chunk<DT>(w0[c * 64], b[c], c0);
-    c1 = mfma_chunk<DT>(w1[c * 64], b[c], c1);
-  }
-  f32x4 acc;
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-    acc[i] = __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(c0[i]), __float_as_int(c1[i]),
-                                                        0x118, 0xF, 0xC, false));
-  tile_epilogue<DT, KMAX>(p, h, acc, l, t, ok && h.row_ok, r);
-}
-
 // Word 0 of slice 0 of the (stage, row) slice records; word w of slice s is
 // at + w * kSlicesMax + s.
 __device__ __forceinline__ uint64_t* slice_record(const Plan& p, int stage, int row) {
@@ -715,27 +705,19 @@ __device__ __forceinline__ uint64_t* slice_record(const Plan& p, int stage, int 
 // lanes' best four keys and the (max, sum) pairs and ends in the record, which
 // is all the keeper needs unless a row's record keys do not settle it; the
 // second then carries the full lists, which only that rare case reads.
-// Rows live in lanes col, col+16, col+32, col+48 of every wave (and, folded,
-// in lanes col and col ^ 8).
-template <int KMAX, int WAVES, bool FOLD = false>
+// Rows live in lanes col, col+16, col+32, col+48 of every wave.
+template <int KMAX, int WAVES>
 __device__ __forceinline__ void publish_partial(const Plan& p, const HeadLane& h, int stage,
                                                 int slice, RowAcc<KMAX>& r,
                                                 HeadShared<KMAX, WAVES>& sh) {
   constexpr int HT = KMAX < 4 ? KMAX : 4;
   const size_t o = ((size_t)stage * p.rows_max + h.row) * kSlicesMax + slice;
-  const bool writer = h.grp == 0 && h.row_ok && h.lead;
+  const bool writer = h.grp == 0 && h.row_ok;
   {
     uint64_t t[HT];
 #pragma unroll
     for (int i = 0; i < HT; ++i) t[i] = r.list[i];
     float m = r.m, sum = r.s;
-    if constexpr (FOLD) {
-      uint64_t x[HT];
-#pragma unroll
-      for (int i = 0; i < HT; ++i) x[i] = dpp64<0x128, 0xF>(t[i]);
-      list_merge(t, x);
-      lse_combine(m, sum, dppf<0x128, 0xF>(m, kNegBig), dppf<0x128, 0xF>(sum, 0.0f));
-    }
     list_merge_pair<16>(t);
     lse_combine_pair<16>(m, sum);
     list_merge_pair<32>(t);
@@ -785,12 +767,6 @@ __device__ __forceinline__ void publish_partial(const Plan& p, const HeadLane& h
     }
   }
   if constexpr (HT < KMAX) {
-    if constexpr (FOLD) {
-      uint64_t x[KMAX];
-#pragma unroll
-      for (int i = 0; i < KMAX; ++i) x[i] = dpp64<0x128, 0xF>(r.list[i]);
-      list_merge(r.list, x);
-    }
     list_merge_pair<16>(r.list);
     list_merge_pair<32>(r.list);
     if (h.grp == 0) {
@@ -886,356 +862,6 @@ __device__ __forceinline__ void head_slice(const Plan& p, int d, int P, int cb, 
   publish_partial<KMAX, WAVES>(p, h, 0, slice, r, sh);
 }
 
-// Tiles a streaming block of the persistent kernel keeps on chip for the
-// whole round: RT per wave in registers and up to LTW per wave in LDS.
-// (64 VGPRs of resident A fragments per lane at most: more spills.)
-__host__ __device__ constexpr int resident_reg_tiles(int ncmax, bool fold = false) {
-  if (fold) return ncmax <= 2 ? 4 : (ncmax <= 4 ? 3 : (ncmax <= 8 ? 3 : 1));
-  return ncmax <= 2 ? 4 : (ncmax <= 4 ? 3 : (ncmax <= 8 ? 2 : 1));
-}
-__host__ __device__ constexpr int resident_lds_tiles_per_wave(int ncmax) {
-  return ncmax <= 4 ? 4 : (ncmax <= 8 ? 2 : 1);
-}
-
-// A streaming block of the persistent kernel.  W of its slice is read from
-// memory once per round: the first RT*WAVES tiles go to registers, the next
-// p.lds_tiles to LDS (stored in MFMA fragment order), and only the rest, if
-// any, is streamed at every stage.  Each stage then loads L_d before waiting
-// for the selector's release, reads the new head input and runs the tiles.
-// ---------------------------------------------------------------------------
-// persistent form: replicated selection
-// ---------------------------------------------------------------------------
-// Every workgroup keeps its own copy of the frontier (identical everywhere:
-// all derive it from the same published partials with the same code).
-struct FrontShared {
-  int tok[kNarrowRows];
-  float score[kNarrowRows];
-};
-
-// Head input of the frontier in LDS: [rows][r] at the head's precision, rows
-// padded by 16 bytes so that the 16 columns' B-fragment reads spread over
-// the banks.
-__device__ __forceinline__ int u_stride(const Plan& p) { return p.r * (p.dtype ? 2 : 4) + 16; }
-
-template <int DT>
-__device__ void compute_u(const Plan& p, const FrontShared& fs, int d, int P, char* ul) {
-  constexpr int Q = 4;  // elements per work item
-  const int rows = p.R * P;
-  const int us = u_stride(p);
-  const int n = rows * p.r / Q;
-  for (int base = 0; base < n; base += 2 * (int)blockDim.x) {
-    uint32_t ev[2][Q];
-    f32x4 hv[2];
-    int urow[2], j0[2];
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const int e = min(base + q * (int)blockDim.x + (int)threadIdx.x, n - 1) * Q;
-      const int row = e / p.r;
-      const int j = e - row * p.r;
-      const int req = row / P;
-      const int tok = min(max(fs.tok[req * p.kk + (row - req * P)], 0), p.V - 1);
-      const size_t eo = (size_t)tok * p.r + j;
-      if (DT) {
-        const u32x2 v = *gmem((const u32x2*)((const uint16_t*)p.E + eo));
-        ev[q][0] = v.x << 16;
-        ev[q][1] = v.x & 0xffff0000u;
-        ev[q][2] = v.y << 16;
-        ev[q][3] = v.y & 0xffff0000u;
-      } else {
-        const u32x4 v = *gmem((const u32x4*)((const float*)p.E + eo));
-#pragma unroll
-        for (int i = 0; i < Q; ++i) ev[q][i] = v[i];
-      }
-      hv[q] = *gmem((const f32x4*)(p.h + ((size_t)req * p.B + d) * p.r + j));
-      urow[q] = row;
-      j0[q] = j;
-    }
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      if (base + q * (int)blockDim.x + (int)threadIdx.x < n) {
-        char* dst = ul + (size_t)urow[q] * us;
-        if (p.mode == 2) {  // parent-independent: zero head input
-          if (DT)
-            *(uint2*)(dst + j0[q] * 2) = uint2{0u, 0u};
-          else
-            *(f32x4*)(dst + j0[q] * 4) = f32x4{0.f, 0.f, 0.f, 0.f};
-        } else if (DT) {
-          uint16_t u[Q];
-#pragma unroll
-          for (int i = 0; i < Q; ++i) u[i] = silu_bf16(__uint_as_float(ev[q][i]), hv[q][i]);
-          uint2 v;
-          v.x = (uint32_t)u[0] | ((uint32_t)u[1] << 16);
-          v.y = (uint32_t)u[2] | ((uint32_t)u[3] << 16);
-          *(uint2*)(dst + j0[q] * 2) = v;
-        } else {
-          float u[Q];
-#pragma unroll
-          for (int i = 0; i < Q; ++i) u[i] = silu_f32(__uint_as_float(ev[q][i]), hv[q][i]);
-          *(f32x4*)(dst + j0[q] * 4) = f32x4{u[0], u[1], u[2], u[3]};
-        }
-      }
-    }
-  }
-  __syncthreads();
-}
-
-// B fragments from the head input in LDS (zero past the rows and the rank).
-template <int DT, int NCMAX>
-__device__ __forceinline__ void load_bfrag_lds(const Plan& p, const HeadLane& h, const char* ul,
-                                               u32x4 (&b)[NCMAX]) {
-  constexpr int KC = DT ? 32 : 16;
-  constexpr int ESZ = DT ? 2 : 4;
-  const char* urow = ul + (size_t)h.col * u_stride(p) + h.grp * (KC / 4) * ESZ;
-#pragma unroll
-  for (int c = 0; c < NCMAX; ++c) {
-    u32x4 v = {0u, 0u, 0u, 0u};
-    if (c < p.nchunk && h.b_ok) v = *(const u32x4*)(urow + c * KC * ESZ);
-    b[c] = v;
-  }
-}
-
-
-template <int DT>
-__device__ __noinline__ void frontier_call(const Plan& lp, int d);
-
-// Wave 0 waits for the stage-d frontier that the keeper publishes (R*k'
-// words, each carrying the call's tag: score bits << 32 | token << kTagBits
-// | tag) and puts its tokens into fs.  Polls with agent-coherent loads,
-// bounded by p.spin_ticks of the device wall clock: returns 0 on a timeout.
-__device__ __forceinline__ int wait_frontier(const Plan& p, int d, FrontShared& fs) {
-  const int lane = threadIdx.x & 63;
-  const int n = p.R * p.kk;  // <= kNarrowRows
-  const uint64_t* src = p.front_w + (size_t)d * p.rows_max + min(lane, n - 1);
-  const long long t0 = wall_clock64();
-  uint64_t w;
-  for (;;) {
-    w = load_agent(src);
-    if (__all(key_tagged(p, w))) break;
-    if (wall_clock64() - t0 > p.spin_ticks) return 0;
-    __builtin_amdgcn_s_sleep(1);
-  }
-  if (lane < n) fs.tok[lane] = min((int)((uint32_t)w >> kTagBits), p.V - 1);
-  return 1;
-}
-
-// Everything a streaming workgroup does before its stage-d stream: wait for
-// the stage-d frontier and build its head input in LDS.  Returns false if
-// the round was abandoned.
-template <int DT, int KMAX>
-__device__ __forceinline__ bool stage_inputs(const Plan& p, const Plan& sp, int d,
-                                             FrontShared& fs, int& sh_go) {
-  if (d > 0) {
-    if (threadIdx.x < 64) {
-      const int ok = wait_frontier(p, d, fs);
-      if (threadIdx.x == 0) sh_go = ok;
-    }
-    __syncthreads();
-    if (!sh_go) return false;
-  }
-  frontier_call<DT>(sp, d);
-  return true;
-}
-
-// The stage-0 frontier: each request's root (token 0 stands in for an invalid
-// one, whose tree is emitted empty).
-__device__ __forceinline__ void init_front(const Plan& p, FrontShared& fs) {
-  for (int i = threadIdx.x; i < p.R * p.kk; i += blockDim.x) {
-    const int root = p.root[i / p.kk];
-    fs.tok[i] = root < 0 || root >= p.V ? 0 : root;
-    fs.score[i] = 0.0f;
-  }
-}
-
-// One streaming workgroup of the persistent round: a fixed V-slice whose W
-// tiles stay on chip (RT per wave in registers, up to LTW per wave in LDS in
-// fragment order, the rest re-read every stage), B stages of frontier
-// selection + head stream + partial publication.
-template <int DT, int NCMAX, int KMAX>
-__device__ __forceinline__ void stream_block(const Plan& p, const Plan& sp, HeadShared<KMAX, kRoundWaves>& sh,
-                             FrontShared& fs, char* ul, u32x4* wl, int& sh_go) {
-  constexpr int WAVES = kRoundWaves;
-  constexpr int RT = resident_reg_tiles(NCMAX);
-  constexpr int LTW = resident_lds_tiles_per_wave(NCMAX);
-  const int slice = blockIdx.x;
-  const int t0 = slice * p.tiles_per_slice;
-  const int t1 = min(t0 + p.tiles_per_slice, p.ntiles);
-  const int nreg = min(t1 - t0, RT * WAVES);
-  const int nlds = min(t1 - t0 - nreg, min(p.lds_tiles, LTW * WAVES));
-  const int lds0 = t0 + nreg;     // first LDS-resident tile
-  const int str0 = lds0 + nlds;   // first streamed tile
-  const int wave = threadIdx.x >> 6;
-  const int lane = threadIdx.x & 63;
-
-  init_front(p, fs);
-  {  // load the resident tiles (the lane geometry of A does not depend on rows)
-    const HeadLane h0(p, 1, 0);
-    u32x4 a[NCMAX];
-    for (int j = wave; j < nlds; j += WAVES) {
-      load_afrag<DT, NCMAX>(p, h0, lds0 + j, a);
-#pragma unroll
-      for (int c = 0; c < NCMAX; ++c) wl[((size_t)j * NCMAX + c) * 64 + lane] = a[c];
-    }
-  }
-  u32x4 areg[RT][NCMAX];
-  {
-    const HeadLane h0(p, 1, 0);
-#pragma unroll
-    for (int i = 0; i < RT; ++i) load_afrag<DT, NCMAX>(p, h0, min(t0 + wave + WAVES * i, t1 - 1), areg[i]);
-  }
-  __syncthreads();
-
-  for (int d = 0; d < p.B; ++d) {
-    const int P = head_rows(p.mode, d, p.kk);
-    const HeadLane h(p, P, 0);
-    // frontier-independent loads before the wait
-    uint32_t lreg[RT][4], llds[LTW][4];
-#pragma unroll
-    for (int i = 0; i < RT; ++i) load_lfrag<DT>(p, h, d, min(t0 + wave + WAVES * i, t1 - 1), lreg[i]);
-#pragma unroll
-    for (int q = 0; q < LTW; ++q)
-      load_lfrag<DT>(p, h, d, min(lds0 + wave + WAVES * q, t1 - 1), llds[q]);
-    TIMELINE_SLICE(d, 0);
-    if (!stage_inputs<DT, KMAX>(p, sp, d, fs, sh_go)) return;
-    TIMELINE_SLICE(d, 1);
-    u32x4 bfrag[NCMAX];
-    load_bfrag_lds<DT, NCMAX>(p, h, ul, bfrag);
-    RowAcc<KMAX> r;
-    r.init();
-#pragma unroll
-    for (int i = 0; i < RT; ++i) {
-      const int t = t0 + wave + WAVES * i;
-      int tt = t;
-      asm volatile("" : "+v"(tt));  // keep the key parts of a resident tile unhoisted
-      if (t < lds0) tile_step<DT, NCMAX, KMAX>(p, h, areg[i], bfrag, lreg[i], tt, r);
-    }
-#pragma unroll
-    for (int q = 0; q < LTW; ++q) {
-      const int j = wave + WAVES * q;
-      if (j < nlds) {
-        u32x4 a[NCMAX];
-#pragma unroll
-        for (int c = 0; c < NCMAX; ++c) a[c] = wl[((size_t)j * NCMAX + c) * 64 + lane];
-        int tt = lds0 + j;
-        asm volatile("" : "+v"(tt));  // (as above)
-        tile_step<DT, NCMAX, KMAX>(p, h, a, bfrag, llds[q], tt, r);
-      }
-    }
-    for (int t = str0 + wave; t < t1; t += WAVES) {
-      Tile<NCMAX> T;
-      load_afrag<DT, NCMAX>(p, h, t, T.a);
-      load_lfrag<DT>(p, h, d, t, T.l);
-      tile_step<DT, NCMAX, KMAX>(p, h, T.a, bfrag, T.l, t, r);
-    }
-    TIMELINE_SLICE(d, 2);
-    publish_partial<KMAX, WAVES>(p, h, d, slice, r, sh);
-    TIMELINE_SLICE(d, 3);
-  }
-}
-
-// stream_block for at most 8 frontier rows: tiles go through the MFMA in
-// pairs whose C fragments are folded into one set of 16 columns (see
-// HeadLane), so every lane's epilogue works on a live row.
-template <int DT, int NCMAX, int KMAX>
-__device__ void stream_block_fold(const Plan& p, const Plan& sp,
-                                  HeadShared<KMAX, kRoundWaves>& sh, FrontShared& fs, char* ul,
-                                  u32x4* wl, int& sh_go) {
-  constexpr int WAVES = kRoundWaves;
-  constexpr int RT = resident_reg_tiles(NCMAX, true);
-  constexpr int LTW = resident_lds_tiles_per_wave(NCMAX);
-  constexpr int RP = (RT + 1) / 2;   // register-resident pairs per wave
-  constexpr int LP = (LTW + 1) / 2;  // LDS-resident pairs per wave
-  const int slice = blockIdx.x;
-  const int t0 = slice * p.tiles_per_slice;
-  const int t1 = min(t0 + p.tiles_per_slice, p.ntiles);
-  const int nreg = min(t1 - t0, RT * WAVES);
-  const int nlds = min(t1 - t0 - nreg, min(p.lds_tiles, LTW * WAVES));
-  const int lds0 = t0 + nreg;
-  const int str0 = lds0 + nlds;
-  const int wave = threadIdx.x >> 6;
-  const int lane = threadIdx.x & 63;
-
-  init_front(p, fs);
-  {
-    const HeadLane h0(p, 1, 0);
-    u32x4 a[NCMAX];
-    for (int j = wave; j < nlds; j += WAVES) {
-      load_afrag<DT, NCMAX>(p, h0, lds0 + j, a);
-#pragma unroll
-      for (int c = 0; c < NCMAX; ++c) wl[((size_t)j * NCMAX + c) * 64 + lane] = a[c];
-    }
-  }
-  u32x4 areg[RT][NCMAX];
-  {
-    const HeadLane h0(p, 1, 0);
-#pragma unroll
-    for (int i = 0; i < RT; ++i) load_afrag<DT, NCMAX>(p, h0, min(t0 + wave + WAVES * i, t1 - 1), areg[i]);
-  }
-  __syncthreads();
-
-  for (int d = 0; d < p.B; ++d) {
-    const int P = head_rows(p.mode, d, p.kk);
-    const HeadLane h(p, P, 0, true);
-    // L_d of the lane's own tile of every resident pair, before the wait
-    uint32_t lreg[RP][4], llds[LP][4];
-#pragma unroll
-    for (int q = 0; q < RP; ++q)
-      load_lfrag<DT>(p, h, d, min(t0 + wave + WAVES * (2 * q + h.half), t1 - 1), lreg[q]);
-#pragma unroll
-    for (int q = 0; q < LP; ++q)
-      load_lfrag<DT>(p, h, d, min(lds0 + wave + WAVES * (2 * q + h.half), t1 - 1), llds[q]);
-    TIMELINE_SLICE(d, 0);
-    if (!stage_inputs<DT, KMAX>(p, sp, d, fs, sh_go)) return;
-    TIMELINE_SLICE(d, 1);
-    u32x4 bfrag[NCMAX];
-    load_bfrag_lds<DT, NCMAX>(p, h, ul, bfrag);
-    RowAcc<KMAX> r;
-    r.init();
-#pragma unroll
-    for (int q = 0; q < RP; ++q) {
-      const int i1 = min(2 * q + 1, RT - 1);
-      const int ta = t0 + wave + WAVES * (2 * q);
-      const int tb = t0 + wave + WAVES * (2 * q + 1);
-      const bool okb = 2 * q + 1 < RT && tb < lds0;
-      // the tile index is the same every stage; hidden from the compiler so
-      // that the token parts of its keys are recomputed (a few VALU ops)
-      // rather than hoisted out of the stage loop and spilled to scratch
-      int tt = h.half ? tb : ta;
-      asm volatile("" : "+v"(tt));
-      if (ta < lds0)
-        tile_pair_step<DT, NCMAX, KMAX>(p, h, areg[2 * q], areg[i1], bfrag, lreg[q], tt,
-                                        h.half ? okb : true, r);
-    }
-#pragma unroll
-    for (int q = 0; q < LP; ++q) {
-      const int ja = wave + WAVES * (2 * q);
-      const int jb = wave + WAVES * (2 * q + 1);
-      if (ja < nlds) {
-        const bool okb = 2 * q + 1 < LTW && jb < nlds;
-        const int jl = okb ? jb : ja;
-        int tt = lds0 + (h.half ? jb : ja);
-        asm volatile("" : "+v"(tt));  // (as above)
-        lds_pair_step<DT, NCMAX, KMAX>(p, h, wl + (size_t)ja * NCMAX * 64 + lane,
-                                       wl + (size_t)jl * NCMAX * 64 + lane, bfrag, llds[q], tt,
-                                       h.half ? okb : true, r);
-      }
-    }
-    for (int ta = str0 + wave; ta < t1; ta += 2 * WAVES) {
-      const int tb = ta + WAVES;
-      const bool okb = tb < t1;
-      const int tl = h.half && okb ? tb : ta;
-      u32x4 a0[NCMAX], a1[NCMAX];
-      uint32_t l[4];
-      load_afrag<DT, NCMAX>(p, h, ta, a0);
-      load_afrag<DT, NCMAX>(p, h, okb ? tb : ta, a1);
-      load_lfrag<DT>(p, h, d, tl, l);
-      tile_pair_step<DT, NCMAX, KMAX>(p, h, a0, a1, bfrag, l, tl, h.half ? okb : true, r);
-    }
-    TIMELINE_SLICE(d, 2);
-    publish_partial<KMAX, WAVES, true>(p, h, d, slice, r, sh);
-    TIMELINE_SLICE(d, 3);
-  }
-}
-
 // ---------------------------------------------------------------------------
 // stage selection on merged rows (shared by both launch forms)
 // ---------------------------------------------------------------------------
@@ -1315,400 +941,187 @@ __device__ __forceinline__ int group_lanes(int n, int nthreads) {
 }
 
 struct SelShared {
-  int next_tok[kNarrowRows];  // tokens of the next frontier, by slot (request-major)
+  int next_tok[kNarrowRows];  // tokens of the next frontier, by slot
   uint64_t rowkeys[kNarrowRows][16];  // top-k' children (child keys) of each row
   float lse[kNarrowRows];
+  uint64_t cword[256];  // (keepers) the candidates' published words
   __attribute__((aligned(16))) uint64_t ckey[256];  // node keys of the stage's candidates
   int rank[256];
-  __attribute__((aligned(16))) uint64_t tkey[PCTREE_EMIT_MAX_N];  // a request's top-N keys
-  __attribute__((aligned(16))) uint64_t sk[256];  // the surviving candidates' keys, by request
+  __attribute__((aligned(16))) uint64_t tkey[PCTREE_EMIT_MAX_N];  // the request's top-N keys
+  __attribute__((aligned(16))) uint64_t sk[256];  // the surviving candidates' keys
   int sci[256];         // and their candidate indices
-  int rstart[17];       // each request's first survivor (and the total after the last)
-  uint32_t tord[16];    // each request's survival threshold (high word of a key)
+  uint32_t tord;        // the survival threshold (high word of a key)
   int wcnt[kSelectThreads / 64];  // survivors per wave
-  int abort;  // a wait of the selection timed out
 };
 
-// Candidates of the P rows of each request in [req0, req0 + nreq), whose
-// top-k' children and lse are in sh.rowkeys / sh.lse (request-major, row 0 =
-// request req0's slot 0): score them (Eq. 4), put them into the pool, pick the
-// next frontier (the k' best of each request's layer, Sec. 4.1), merge them
-// into the running global top-N (Sec. 4.2) and write the next head input.
-// Needs blockDim >= 512 and nreq * P * k' <= 256.  `mid` runs (all threads)
-// once the next frontier is in sh.next_tok and the pool entries are stored,
-// before the top-N merge: a caller issues the next stage's loads there.
+// One stage's selection of request req on P frontier parents: score the
+// candidates (Eq. 4), put them into the pool, pick the next frontier (the k'
+// best of the layer, Sec. 4.1) and merge them into the running global top-N
+// (Sec. 4.2).  WORDS: the candidates come as the mergers' words in sh.cword
+// (in the control modes with their log-probability instead of the path
+// score); otherwise from the rows' top-k' children and lse in sh.rowkeys /
+// sh.lse.  shared: one row serves every parent.  Needs blockDim >= 512 and
+// P * k' <= 256.  `mid` runs (all threads) once the next frontier is in
+// sh.next_tok and the pool entries are stored, before the top-N merge: a
+// caller issues the next stage's loads there.
 struct NoMid {
   __device__ void operator()() const {}
 };
-template <class Mid = NoMid>
+template <bool WORDS, class Mid = NoMid>
 __device__ __forceinline__ void stage_select_body(const Plan& p, const State& st, int d, int P,
-                                                  int req0, int nreq, SelShared& sh,
-                                                  bool bcast, bool shared, Mid mid = Mid()) {
+                                                  int req, SelShared& sh, bool shared,
+                                                  Mid mid = Mid()) {
   const int tid = threadIdx.x;
   const int kk = p.kk;
-  const int per_req = P * kk;
-  const int ncand = nreq * per_req;
+  const int ncand = P * kk;
   const int nbase = d == 0 ? 1 : 1 + kk + (d - 1) * kk * kk;  // pool id of the first candidate
   const bool more = d + 1 < p.B;
 
-  int tok = 0, par = 0;
+  int tok = 0, par = 0, pr = 0;
   float score = 0.0f;
   if (tid < ncand) {
-    const int rq = tid / per_req;
-    const int ci = tid - rq * per_req;
-    const int pr = ci / kk;
-    const int j = ci - pr * kk;
-    const int req = req0 + rq;
-    const int lrow = shared ? rq : rq * P + pr;  // shared: one row serves every parent
-    const uint64_t ck = sh.rowkeys[lrow][j];
-    // every row holds >= k' real keys (V >= k'); the clamp only keeps a
-    // corrupted key from indexing out of bounds
-    tok = min(max(child_key_token(ck), 0), p.V - 1);
-    const float lp = child_key_value(ck) - sh.lse[lrow];
-    score = st.front_score[(req - st.rbase) * kk + pr] + lp;
+    pr = tid / kk;
+    const int j = tid - pr * kk;
+    const int lrow = shared ? 0 : pr;
+    const float front = st.front_score[(req - st.rbase) * kk + pr];
+    if constexpr (WORDS) {
+      const uint64_t w = sh.cword[lrow * kk + j];
+      tok = min((int)((uint32_t)w >> kTagBits), p.V - 1);
+      const float v = __uint_as_float((uint32_t)(w >> 32));
+      score = shared ? front + v : v;
+    } else {
+      const uint64_t ck = sh.rowkeys[lrow][j];
+      // every row holds >= k' real keys (V >= k'); the clamp only keeps a
+      // corrupted key from indexing out of bounds
+      tok = min(max(child_key_token(ck), 0), p.V - 1);
+      const float lp = child_key_value(ck) - sh.lse[lrow];
+      score = front + lp;
+    }
     par = st.front_node[(req - st.rbase) * kk + pr];
     sh.ckey[tid] = node_key(score, d + 1, tok, pr);
   }
   // (the frontier's loads above have returned: LDS barriers suffice until
   // the frontier is rewritten)
   lds_barrier();
-  // With many candidates per request (config-sized layers of 128 and up),
-  // only those that can still enter the next frontier or the running top-N
-  // are ranked.  A parent's children are sorted, so its first child scores
-  // highest; with P >= k' parents, the k' best candidates all score at
-  // least the lowest of those P firsts.  A candidate entering a full top-N
-  // scores at least its last entry.  Candidates scoring below both
-  // thresholds (compared on the key's high word, the ordered score) are
-  // dropped; every survivor's rank among all candidates equals its rank
-  // among the survivors, and every dropped one ranks below every survivor
-  // and every top-N entry.  Smaller layers are ranked whole, one thread per
-  // candidate (the pruning's extra barriers cost more than they save).
+  // With many candidates (config-sized layers of 128 and up), only those that
+  // can still enter the next frontier or the running top-N are ranked.  A
+  // parent's children are sorted, so its first child scores highest; with
+  // P >= k' parents, the k' best candidates all score at least the lowest of
+  // those P firsts.  A candidate entering a full top-N scores at least its
+  // last entry.  Candidates scoring below both thresholds (compared on the
+  // key's high word, the ordered score) are dropped; every survivor's rank
+  // among all candidates equals its rank among the survivors, and every
+  // dropped one ranks below every survivor and every top-N entry.  Smaller
+  // layers are ranked whole, one thread per candidate (the pruning's extra
+  // barriers cost more than they save).
   const int ncur = min(p.N, nbase);
-  const bool prune = per_req >= 128;
+  const bool prune = ncand >= 128;
+  int total = ncand;
   if (prune) {
-    if (tid < nreq) {
+    if (tid == 0) {
       uint32_t tf = more ? 0u : 0xFFFFFFFFu;
       if (more && P >= kk) {
         tf = 0xFFFFFFFFu;
-        for (int pr = 0; pr < P; ++pr)
-          tf = min(tf, (uint32_t)(sh.ckey[tid * per_req + pr * kk] >> 32));
+        for (int q = 0; q < P; ++q) tf = min(tf, (uint32_t)(sh.ckey[q * kk] >> 32));
       }
       const uint32_t tn =
-          ncur == p.N
-              ? (uint32_t)(st.top_key[(size_t)(req0 + tid - st.rbase) * p.N + p.N - 1] >> 32)
-              : 0u;
-      sh.tord[tid] = min(tf, tn);
+          ncur == p.N ? (uint32_t)(st.top_key[(size_t)(req - st.rbase) * p.N + p.N - 1] >> 32)
+                      : 0u;
+      sh.tord = min(tf, tn);
     }
     lds_barrier();
-    // the survivors, compacted in candidate order (so each request's are
-    // contiguous): wave counts, then each lane's exclusive prefix
+    // the survivors, compacted in candidate order: wave counts, then each
+    // lane's exclusive prefix
     const int lane = tid & 63, wave = tid >> 6;
-    const bool surv = tid < ncand && (uint32_t)(sh.ckey[tid] >> 32) >= sh.tord[tid / per_req];
+    const bool surv = tid < ncand && (uint32_t)(sh.ckey[tid] >> 32) >= sh.tord;
     const uint64_t bal = __ballot(surv);
     if (lane == 0) sh.wcnt[wave] = __popcll(bal);
     lds_barrier();
-    int total = 0, base = 0;
+    total = 0;
+    int base = 0;
     for (int w = 0; w < (ncand + 63) / 64; ++w) {
       const int c = sh.wcnt[w];
       base += w < wave ? c : 0;
       total += c;
     }
     if (tid < ncand) {
-      const int pos = base + __popcll(bal & ((1ull << lane) - 1));
       if (surv) {
+        const int pos = base + __popcll(bal & ((1ull << lane) - 1));
         sh.sk[pos] = sh.ckey[tid];
         sh.sci[pos] = tid;
       }
       sh.rank[tid] = 0x7FFFFFFF;  // (a survivor's is set below)
-      if (tid % per_req == 0) sh.rstart[tid / per_req] = pos;
     }
-    if (tid == 0) sh.rstart[nreq] = total;
     lds_barrier();
-    // each survivor's rank among its request's survivors, T lanes each
+    // each survivor's rank among the survivors, T lanes each
     const int T = group_lanes(total, blockDim.x);
     const int e = tid / T;
     const bool live = e < total;
-    const int c = live ? sh.sci[e] : 0;
-    const int s0 = sh.rstart[c / per_req];
-    const int n = live ? sh.rstart[c / per_req + 1] - s0 : 0;
-    const int cnt = count_greater_group(sh.sk + s0, n, live ? sh.sk[e] : 0, tid & (T - 1), T);
-    if (live && (tid & (T - 1)) == 0) sh.rank[c] = cnt;
+    const int cnt =
+        count_greater_group(sh.sk, live ? total : 0, live ? sh.sk[e] : 0, tid & (T - 1), T);
+    if (live && (tid & (T - 1)) == 0) sh.rank[sh.sci[e]] = cnt;
   } else if (tid < ncand) {
-    const int rq = tid / per_req;
-    sh.rank[tid] = count_greater(sh.ckey + rq * per_req, per_req, sh.ckey[tid]);
+    sh.rank[tid] = count_greater(sh.ckey, ncand, sh.ckey[tid]);
   }
   lds_barrier();
   // next frontier (every frontier slot was read above, before the barriers)
   if (more && tid < ncand && sh.rank[tid] < kk) {
-    const int rq = tid / per_req;
-    const int ci = tid - rq * per_req;
-    const int req = req0 + rq;
     const int slot = sh.rank[tid];
-    if (bcast) {  // the streaming workgroups wait for these words
-      // (with one shared row, the next row's token is the greedy chain's:
-      // the row's best child, which slot 0 carries)
-      const int wtok = shared ? min(max(child_key_token(sh.rowkeys[rq][0]), 0), p.V - 1) : tok;
-      __hip_atomic_store(p.front_w + (size_t)(d + 1) * p.rows_max + req * kk + slot,
-                         ((uint64_t)__float_as_uint(score) << 32) |
-                             ((uint64_t)wtok << kTagBits) | p.tag,
-                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    st.front_node[(req - st.rbase) * kk + slot] = nbase + ci;
+    st.front_node[(req - st.rbase) * kk + slot] = nbase + tid;
     st.front_tok[(req - st.rbase) * kk + slot] = tok;
     st.front_score[(req - st.rbase) * kk + slot] = score;
-    if (rq * kk + slot < kNarrowRows) sh.next_tok[rq * kk + slot] = tok;
+    sh.next_tok[slot] = tok;
     if (p.t_token) {
       const size_t o = ((size_t)req * p.B + d + 1) * p.k + slot;
       p.t_token[o] = tok;
-      p.t_pslot[o] = ci / kk;
+      p.t_pslot[o] = pr;
       p.t_score[o] = score;
     }
   }
   // the pool entries of the stage's candidates
   if (tid < ncand) {
-    const int rq = tid / per_req;
-    const size_t id = (size_t)(req0 + rq) * p.maxpool + nbase + (tid - rq * per_req);
+    const size_t id = (size_t)req * p.maxpool + nbase + tid;
     p.node_tok[id] = tok;
     p.node_par[id] = par;
     p.node_depth[id] = d + 1;
     p.node_score[id] = score;
   }
   mid();
-  // running global top-N, one request at a time: every element's new
-  // position is its rank in the union (both sides are sorted), computed
-  // before any element moves.  The state is in LDS (every caller keeps a
-  // copy there), so LDS barriers order it; the global stores above need no
-  // wait until the barrier that ends the stage.
-  for (int rq = 0; rq < nreq; ++rq) {
-    const int req = req0 + rq;
-    uint64_t* tk = st.top_key + (size_t)(req - st.rbase) * p.N;
-    int* tn = st.top_node + (size_t)(req - st.rbase) * p.N;
-    lds_barrier();
-    for (int i = tid; i < ncur; i += blockDim.x) sh.tkey[i] = tk[i];
-    lds_barrier();
-    // the request's candidates: its survivors, or all of them
-    const int s0 = prune ? sh.rstart[rq] : rq * per_req;
-    const int ns = prune ? sh.rstart[rq + 1] - s0 : per_req;
-    const uint64_t* keys = prune ? sh.sk : sh.ckey;
-    int pos = p.N, node = 0;
-    uint64_t key = 0;
-    if (tid < ns) {
-      const int c = prune ? sh.sci[s0 + tid] : s0 + tid;
-      key = keys[s0 + tid];
-      pos = sh.rank[c] + count_greater_desc(sh.tkey, ncur, key);  // (the top-N is sorted)
-      node = nbase + c - rq * per_req;
-    } else if (tid >= 256 && tid < 256 + ncur) {
-      const int i = tid - 256;
-      key = sh.tkey[i];
-      pos = i + count_greater(keys + s0, ns, key);
-      node = tn[i];
-    }
-    lds_barrier();
-    if (pos < p.N) {
-      tk[pos] = key;
-      tn[pos] = node;
-    }
+  // running global top-N: every element's new position is its rank in the
+  // union (both sides are sorted), computed before any element moves.  The
+  // state is in LDS (every caller keeps a copy there), so LDS barriers order
+  // it; the global stores above need no wait until the barrier that ends the
+  // stage.
+  uint64_t* tk = st.top_key + (size_t)(req - st.rbase) * p.N;
+  int* tn = st.top_node + (size_t)(req - st.rbase) * p.N;
+  lds_barrier();
+  for (int i = tid; i < ncur; i += blockDim.x) sh.tkey[i] = tk[i];
+  lds_barrier();
+  // the request's candidates: its survivors, or all of them
+  const uint64_t* keys = prune ? sh.sk : sh.ckey;
+  int pos = p.N, node = 0;
+  uint64_t key = 0;
+  if (tid < total) {
+    const int c = prune ? sh.sci[tid] : tid;
+    key = keys[tid];
+    pos = sh.rank[c] + count_greater_desc(sh.tkey, ncur, key);  // (the top-N is sorted)
+    node = nbase + c;
+  } else if (tid >= 256 && tid < 256 + ncur) {
+    const int i = tid - 256;
+    key = sh.tkey[i];
+    pos = i + count_greater(keys, total, key);
+    node = tn[i];
+  }
+  lds_barrier();
+  if (pos < p.N) {
+    tk[pos] = key;
+    tn[pos] = node;
   }
   // (the stage's global stores, pool entries and trace, are read by later
   // launches or, in the persistent form, by the emission after a full
   // barrier: an LDS barrier ends the stage)
   lds_barrier();
 }
-
-// The stage, init and emission routines have an out-of-line entry (used by the
-// multi-launch kernels and the k' <= 8 keepers) and an inlined body: a keeper
-// with k' = 16 that called them out of line kept a copy of its launch
-// arguments in scratch memory, so it inlines the bodies instead.
-__device__ void stage_select(const Plan& p, const State& st, int d, int P, int req0, int nreq,
-                             SelShared& sh, bool bcast, bool shared = false) {
-  stage_select_body(p, st, d, P, req0, nreq, sh, bcast, shared);
-}
-
-// The top-k' children and the lse of each of the R*P (<= 16) rows of stage d
-// from the published slice partials, one wave per row, as the words land:
-// every word carries the call's tag, so the wave re-reads (agent-coherent
-// loads) the records that are not complete yet until all are.  Every slice's
-// record holds its kHeadKeys best keys and its sum of exp: k' pops of the
-// wave-wide maximum over the union of those keys give the row's top-k' unless
-// some slice gave up all of its record keys (it may hold more that belong).
-// Then, and only then, the lists are read: a row's top-k' lie in the k'
-// slices with the largest best keys (any other slice is beaten k' times
-// over), and k' pops over those lists give the exact answer.  Keys are unique
-// (the token is part of them), so each pop removes exactly one entry.
-// Returns false if a wait ran past p.spin_ticks (the round is abandoned).
-template <int KMAX, int HPL>
-__device__ __forceinline__ bool sel_merge_rows(const Plan& p, int d, int rows, SelShared& sh) {
-  constexpr int HK = KMAX < kHeadKeys ? KMAX : kHeadKeys;  // record keys that can be real
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const int nwave = blockDim.x >> 6;
-  const int G = p.G;
-  const int kk = p.kk;
-  bool alive = true;
-  for (int row = wave; row < rows && alive; row += nwave) {
-    const size_t base = ((size_t)d * p.rows_max + row) * kSlicesMax;
-    const uint64_t* recs = slice_record(p, d, row);
-    uint64_t hk[HPL][HK], first[HPL];
-    float hs[HPL];
-    bool have[HPL];
-#pragma unroll
-    for (int c = 0; c < HPL; ++c) {
-      have[c] = lane + 64 * c >= G;  // no slice: nothing to wait for
-#pragma unroll
-      for (int i = 0; i < HK; ++i) hk[c][i] = 0;
-      hs[c] = 0.0f;
-    }
-    const long long t0 = wall_clock64();
-    for (;;) {
-#pragma unroll
-      for (int c = 0; c < HPL; ++c) {
-        if (!have[c]) {
-          const uint64_t* rec = recs + lane + 64 * c;
-          uint64_t w[kRecWords];
-#pragma unroll
-          for (int i = 0; i < kRecWords; ++i) w[i] = load_agent(rec + i * kSlicesMax);
-          bool ok = sum_tagged(p, w[kHeadKeys]);
-#pragma unroll
-          for (int i = 0; i < kHeadKeys; ++i) ok = ok && key_tagged(p, w[i]);
-          have[c] = ok;
-#pragma unroll
-          for (int i = 0; i < HK; ++i) hk[c][i] = w[i];
-          hs[c] = __uint_as_float((uint32_t)w[kHeadKeys]);
-        }
-      }
-      bool all = true;
-#pragma unroll
-      for (int c = 0; c < HPL; ++c) all = all && have[c];
-      if (__all(all)) break;
-      if (wall_clock64() - t0 > p.spin_ticks) {
-        alive = false;
-        break;
-      }
-      __builtin_amdgcn_s_sleep(1);
-    }
-    if (!alive) break;
-    // lse over the slices: each sum is relative to the slice's best logit
-    float m = kNegBig, s = 0.0f;
-#pragma unroll
-    for (int c = 0; c < HPL; ++c) {
-      first[c] = hk[c][0];
-      if (lane + 64 * c < G) lse_combine(m, s, child_key_value(hk[c][0]), hs[c]);
-    }
-    const float M = wave_max_f32(m);
-    const float S = wave_sum_f32(s * exp2_raw((m - M) * kLog2e));
-    int used[HPL];
-#pragma unroll
-    for (int c = 0; c < HPL; ++c) used[c] = 0;
-#pragma unroll
-    for (int it = 0; it < KMAX; ++it) {
-      if (it < kk) {
-        uint64_t lm = hk[0][0];
-#pragma unroll
-        for (int c = 1; c < HPL; ++c) lm = key_max(lm, hk[c][0]);
-        const uint64_t best = wave_max_u64(lm);
-#pragma unroll
-        for (int c = 0; c < HPL; ++c) {
-          if (hk[c][0] == best) {
-#pragma unroll
-            for (int i = 0; i + 1 < HK; ++i) hk[c][i] = hk[c][i + 1];
-            hk[c][HK - 1] = 0;
-            ++used[c];
-          }
-        }
-        if (lane == 0) sh.rowkeys[row][it] = best;
-      }
-    }
-    // (pops past the union's real keys return 0 and count for every empty
-    // entry, so a slice's count can pass HK)
-    bool gave_all = false;
-    if (HK < KMAX) {
-#pragma unroll
-      for (int c = 0; c < HPL; ++c) gave_all = gave_all || used[c] >= HK;
-    }
-    if (__any(gave_all)) {
-      // the k' largest best keys; lane i keeps the slice of the i-th
-      const int nwin = min(kk, G);
-#pragma unroll
-      for (int c = 1; c < HPL; ++c) {
-#pragma unroll
-        for (int i = c; i > 0; --i) {
-          const uint64_t a = first[i - 1], b = first[i];
-          const bool sw = b > a;
-          first[i - 1] = sw ? b : a;
-          first[i] = sw ? a : b;
-        }
-      }
-      uint64_t won = 0;
-#pragma unroll
-      for (int it = 0; it < KMAX; ++it) {
-        if (it < nwin) {
-          const uint64_t best = wave_max_u64(first[0]);
-          if (first[0] == best) {
-#pragma unroll
-            for (int c = 0; c + 1 < HPL; ++c) first[c] = first[c + 1];
-            first[HPL - 1] = 0;
-          }
-          if (lane == it) won = best;
-        }
-      }
-      const int myslice =
-          lane < nwin ? min(child_key_token(won) / (p.tiles_per_slice * kTile), G - 1) : 0;
-      const uint64_t* src = p.part_key + (base + myslice) * KMAX;
-      uint64_t lst[KMAX];
-#pragma unroll
-      for (int i = 0; i < KMAX; ++i) lst[i] = 0;
-      bool got = lane >= nwin;
-      const long long t1 = wall_clock64();
-      for (;;) {
-        if (!got) {
-          bool ok = true;
-#pragma unroll
-          for (int i = 0; i < KMAX; ++i) {
-            lst[i] = load_agent(src + i);
-            ok = ok && key_tagged(p, lst[i]);
-          }
-          got = ok;
-        }
-        if (__all(got)) break;
-        if (wall_clock64() - t1 > p.spin_ticks) {
-          alive = false;
-          break;
-        }
-        __builtin_amdgcn_s_sleep(1);
-      }
-      if (!alive) break;
-      if (lane >= nwin) {
-#pragma unroll
-        for (int i = 0; i < KMAX; ++i) lst[i] = 0;
-      }
-#pragma unroll
-      for (int it = 0; it < KMAX; ++it) {
-        if (it < kk) {
-          const uint64_t best = wave_max_u64(lst[0]);
-          if (lst[0] == best) {
-#pragma unroll
-            for (int i = 0; i + 1 < KMAX; ++i) lst[i] = lst[i + 1];
-            lst[KMAX - 1] = 0;
-          }
-          if (lane == 0) sh.rowkeys[row][it] = best;
-        }
-      }
-    }
-    if (lane == 0) sh.lse[row] = M + logf(S);
-  }
-  if (!alive && lane == 0) sh.abort = 1;
-  __syncthreads();
-  return sh.abort == 0;
-}
-
-// The persistent form uses at most kRoundSlicesMax slices (one per CU).
-template <int KMAX>
-__device__ __forceinline__ bool sel_merge(const Plan& p, int d, int rows, SelShared& sh) {
-  if (p.G <= 64) return sel_merge_rows<KMAX, 1>(p, d, rows, sh);
-  if (p.G <= 128) return sel_merge_rows<KMAX, 2>(p, d, rows, sh);
-  return sel_merge_rows<KMAX, kRoundSlicesMax / 64>(p, d, rows, sh);
-}
-
 
 // ---------------------------------------------------------------------------
 // emission in canonical order (+ optional ancestor mask)
@@ -1745,15 +1158,18 @@ __device__ void mask_rows(const int* par, int count, int N, uint32_t* out, uint3
 // every time).  The ancestor mask row of a node is its parent's row (done a
 // level earlier) plus its own bit.  Uses threads [0, 256) of the block
 // (N <= 256); all threads must call it.
-__device__ __forceinline__ void emit_request_body(const Plan& p, const State& st, int req) {
-  constexpr int kBatch = 8;
-  __shared__ int sh_node[kEmitThreads], sh_emit[kEmitThreads];
-  __shared__ int sh_td[kEmitThreads];     // depth << 20 | token
-  __shared__ uint32_t sh_lkey[kEmitThreads];  // level keys, by level slot
-  __shared__ int lev_cnt[64], lev_off[65], lev_fill[64];
-  __shared__ int sh_maxdep;
-  __shared__ uint32_t sh_words[kEmitThreads * (PCTREE_EMIT_MAX_N / 32)];  // mask rows
+struct EmitShared {
+  int node[kEmitThreads], emit[kEmitThreads];
+  int td[kEmitThreads];         // depth << 20 | token
+  uint32_t lkey[kEmitThreads];  // level keys, by level slot
+  int lev_cnt[64], lev_off[65], lev_fill[64];
+  int maxdep;
+  uint32_t words[kEmitThreads * (PCTREE_EMIT_MAX_N / 32)];  // mask rows
+};
 
+__device__ __forceinline__ void emit_request(const Plan& p, const State& st, int req,
+                                             EmitShared& es) {
+  constexpr int kBatch = 8;
   const int tid = threadIdx.x;
   const int kk = p.kk;
   const int pool = 1 + kk + (p.B - 1) * kk * kk;
@@ -1778,27 +1194,27 @@ __device__ __forceinline__ void emit_request_body(const Plan& p, const State& st
 
   __syncthreads();
   if (tid < 64) {
-    lev_cnt[tid] = 0;
-    lev_fill[tid] = 0;
+    es.lev_cnt[tid] = 0;
+    es.lev_fill[tid] = 0;
   }
-  if (tid == 0) sh_maxdep = -1;
+  if (tid == 0) es.maxdep = -1;
   __syncthreads();
   const bool mine = tid < count;
   if (mine) {
     dep = min(max(dep, 0), p.B);
-    sh_node[tid] = node;
-    sh_td[tid] = (dep << 20) | (tok & 0xFFFFF);
-    atomicAdd(&lev_cnt[dep], 1);
-    atomicMax(&sh_maxdep, dep);
+    es.node[tid] = node;
+    es.td[tid] = (dep << 20) | (tok & 0xFFFFF);
+    atomicAdd(&es.lev_cnt[dep], 1);
+    atomicMax(&es.maxdep, dep);
   }
   __syncthreads();
   if (tid == 0) {
     int acc = 0;
     for (int l = 0; l <= p.B; ++l) {
-      lev_off[l] = acc;
-      acc += lev_cnt[l];
+      es.lev_off[l] = acc;
+      acc += es.lev_cnt[l];
     }
-    lev_off[p.B + 1] = acc;
+    es.lev_off[p.B + 1] = acc;
   }
   // the parent among the selected nodes one level up (-1: none)
   int pidx = -1;
@@ -1809,46 +1225,46 @@ __device__ __forceinline__ void emit_request_body(const Plan& p, const State& st
 #pragma unroll
       for (int i = 0; i < kBatch; ++i) {
         const int j = min(j0 + i, count - 1);
-        nd[i] = sh_node[j];
-        td[i] = sh_td[j];
+        nd[i] = es.node[j];
+        td[i] = es.td[j];
       }
 #pragma unroll
       for (int i = 0; i < kBatch; ++i)
         if (j0 + i < count && nd[i] == pnode && (td[i] & ~0xFFFFF) == want) pidx = j0 + i;
     }
   }
-  __syncthreads();  // lev_off
-  const int myslot = mine ? lev_off[dep] + atomicAdd(&lev_fill[dep], 1) : -1;
+  __syncthreads();  // es.lev_off
+  const int myslot = mine ? es.lev_off[dep] + atomicAdd(&es.lev_fill[dep], 1) : -1;
 
   int emit = -1, pemit = -1;
-  const int maxdep = sh_maxdep;
+  const int maxdep = es.maxdep;
   constexpr int MW = PCTREE_EMIT_MAX_N / 32;  // mask words of a row in LDS
   const int nw = (p.N + 31) / 32;
   for (int l = 0; l <= maxdep; ++l) {
     const bool here = mine && dep == l;
     uint32_t key = 0;
     if (here) {
-      pemit = pidx >= 0 ? sh_emit[pidx] : -1;
+      pemit = pidx >= 0 ? es.emit[pidx] : -1;
       key = ((uint32_t)(pemit + 1) << 20) | (uint32_t)(tok & 0xFFFFF);
-      sh_lkey[myslot] = key;
+      es.lkey[myslot] = key;
     }
     __syncthreads();
     if (here) {
-      const int q0 = lev_off[l], q1 = lev_off[l + 1];
+      const int q0 = es.lev_off[l], q1 = es.lev_off[l + 1];
       int rank = 0;
       for (int q = q0; q < q1; q += kBatch) {
         uint32_t k8[kBatch];
 #pragma unroll
-        for (int i = 0; i < kBatch; ++i) k8[i] = sh_lkey[min(q + i, q1 - 1)];
+        for (int i = 0; i < kBatch; ++i) k8[i] = es.lkey[min(q + i, q1 - 1)];
 #pragma unroll
         for (int i = 0; i < kBatch; ++i) rank += (q + i < q1) && k8[i] < key;
       }
       emit = q0 + rank;
-      sh_emit[tid] = emit;
+      es.emit[tid] = emit;
       if (p.o_mask) {
         for (int w = 0; w < nw; ++w) {
-          const uint32_t up = pemit >= 0 ? sh_words[pemit * MW + w] : 0u;
-          sh_words[emit * MW + w] = up | (w == (emit >> 5) ? 1u << (emit & 31) : 0u);
+          const uint32_t up = pemit >= 0 ? es.words[pemit * MW + w] : 0u;
+          es.words[emit * MW + w] = up | (w == (emit >> 5) ? 1u << (emit & 31) : 0u);
         }
       }
     }
@@ -1874,143 +1290,1148 @@ __device__ __forceinline__ void emit_request_body(const Plan& p, const State& st
   if (p.o_mask) {
     uint32_t* out = p.o_mask + (size_t)req * p.N * nw;
     for (int e = tid; e < p.N; e += blockDim.x)
-      for (int w = 0; w < nw; ++w) out[(size_t)e * nw + w] = e < count ? sh_words[e * MW + w] : 0u;
+      for (int w = 0; w < nw; ++w) out[(size_t)e * nw + w] = e < count ? es.words[e * MW + w] : 0u;
   }
   __syncthreads();
 }
 
-__device__ void emit_request(const Plan& p, const State& st, int req) {
-  emit_request_body(p, st, req);
-}
-
-// An abandoned round (a bounded wait ran out): every output row of every
+// An abandoned round (a bounded wait ran out): every output row of the
 // request is written as padding, mask rows zero, and count = -1 marks the
 // abort, so that nothing of an earlier call's tree is left behind.  All
 // threads of the workgroup take part.
-__device__ __forceinline__ void abort_outputs(const Plan& p) {
-  const int n = p.R * p.N;
-  for (int e = threadIdx.x; e < n; e += blockDim.x) {
-    p.o_token[e] = -1;
-    p.o_parent[e] = -1;
-    p.o_depth[e] = -1;
-    p.o_position[e] = -1;
-    p.o_logprob[e] = -INFINITY;
+__device__ __forceinline__ void abort_outputs(const Plan& p, int req) {
+  const size_t ob = (size_t)req * p.N;
+  for (int e = threadIdx.x; e < p.N; e += blockDim.x) {
+    p.o_token[ob + e] = -1;
+    p.o_parent[ob + e] = -1;
+    p.o_depth[ob + e] = -1;
+    p.o_position[ob + e] = -1;
+    p.o_logprob[ob + e] = -INFINITY;
   }
   if (p.o_mask) {
-    const size_t nw = (size_t)n * ((p.N + 31) / 32);
-    for (size_t e = threadIdx.x; e < nw; e += blockDim.x) p.o_mask[e] = 0u;
+    const int nw = p.N * ((p.N + 31) / 32);
+    for (int e = threadIdx.x; e < nw; e += blockDim.x) p.o_mask[(size_t)req * nw + e] = 0u;
   }
-  for (int req = threadIdx.x; req < p.R; req += blockDim.x) p.o_count[req] = -1;
+  if (threadIdx.x == 0) p.o_count[req] = -1;
 }
 
-// LDS of the persistent round kernel shared by its stage code.
-__shared__ SelShared g_sel;
-__shared__ FrontShared g_front;
-// dynamic LDS: the frontier's head input (streaming blocks), the keeper's
-// running top-N, the streaming blocks' resident W tiles
-extern __shared__ uint64_t g_dyn[];
+// 16 bytes per lane from global memory straight into LDS (lane l's bytes at
+// lds_dst + 16 l), counted in vmcnt like any vector-memory load.  Issued as
+// inline assembly: the compiler does not see the LDS write, so it does not
+// make later LDS reads wait for every load in flight (it cannot tell ring
+// slots apart); the kernel orders them itself with wait_vmcnt and a
+// barrier.  M0 holds the LDS base; nothing else in the kernels that use it
+// keeps a value in M0 across it.
+__device__ __forceinline__ void load_lds16(const void* src, const void* lds_dst) {
+  const uint32_t base = __builtin_amdgcn_readfirstlane(
+      (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)lds_dst);
+  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(base)
+               : "memory", "m0");
+}
 
-// The plan in scalar registers (read from its LDS copy): uniform loop bounds
-// and addresses in the out-of-line stage code below.
-__device__ __forceinline__ Plan scalar_plan(const Plan& lp) {
-  static_assert(sizeof(Plan) % 4 == 0, "Plan is copied word by word");
-  Plan p;
+// s_waitcnt with only the vector-memory count limited (gfx9 encoding:
+// vmcnt bits 3:0 and 15:14, expcnt and lgkmcnt left at their maxima).
+template <int N>
+__device__ __forceinline__ void wait_vmcnt() {
+  static_assert(N >= 0 && N < 64, "vmcnt is 6 bits");
+  __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | 0x0F70);
+}
+
+// ---------------------------------------------------------------------------
+// persistent form: one launch per round
+// ---------------------------------------------------------------------------
+// Workgroups [0, G) stream one V-slice each, the next p.nmerge merge rows and
+// the last R keep one request's tree each.  A stage has two exchanges:
+//  1. every streaming workgroup publishes a record per row (its slice's best
+//     keys and its sum of exp), which the row's merger waits for;
+//  2. the merger publishes the row's k' children as tagged words (path score,
+//     token); every streaming workgroup and every merger waits for all rows'
+//     words and ranks them into the next frontier itself (the same code on the
+//     same words, so the same frontier everywhere), and the request's keeper
+//     keeps the pool, the trace and the running top-N from them, off that path.
+// A stage is bound by the latency of this chain and not by bandwidth (W stays
+// on chip).  What set the split: one keeper that merged all rows read 64 KB of
+// records through one CU and took 5 us to publish the frontier; a merger per
+// row (two with more than 8 rows) reads 8 KB, and the frontier needs no third
+// exchange because ranking 64 words costs a workgroup less than waiting for
+// one more word.
+//
+// W tiles are dealt to slices in turn (slice g owns tiles g, g + G, ...): the
+// likely tokens of a vocabulary have low ids, and a slice holding many of a
+// row's best tokens would make the merger read its full list.
+constexpr int kBatchTiles = 5;                        // tiles per wave of one logit batch
+constexpr int kZTiles = kBatchTiles * kRoundWaves;    // tiles whose logits LDS holds
+constexpr int kZPer = kZTiles * kTile / 64;           // logits of a row per lane
+constexpr int kZStride = kZTiles * kTile + 16;        // floats between rows (16 banks apart)
+
+// Tiles of a wave kept in registers for the whole round: at most 192 VGPRs of
+// A fragments (the rest of the wave's 256 hold accumulators and the row
+// phase); the slice's other tiles are kept in LDS as far as they fit and are
+// read again every stage only past that.
+__host__ __device__ constexpr int resident_reg_tiles(int ncmax) {
+  return ncmax <= 4 ? 5 : (ncmax <= 8 ? 4 : (ncmax <= 12 ? 3 : 2));
+}
+
+// Head input of the frontier in LDS: rows of ncmax chunks (zero past the
+// rank), padded by 16 bytes so that the rows' B-fragment reads spread over
+// the banks.
+__host__ __device__ constexpr int u_stride(int ncmax) { return ncmax * 64 + 16; }
+__host__ __device__ constexpr int round_rows(bool r8) { return r8 ? 8 : kNarrowRows; }
+// Dynamic LDS of a streaming workgroup before its W tiles: head input, logits.
+__host__ __device__ constexpr int round_tile_offset(int ncmax, bool r8) {
+  return round_rows(r8) * (u_stride(ncmax) + kZStride * (int)sizeof(float));
+}
+
+// The stage's frontier, as every streaming workgroup and merger derives it.
+struct FrontShared {
+  __attribute__((aligned(16))) uint64_t sk[256];  // node keys of the candidates
+  int tok[kNarrowRows];      // token of each head row
+  float score[kNarrowRows];  // path score of each frontier node
+  uint32_t first[kNarrowRows];
+  double tab[kSiluTab];
+  int nsurv;
+  int go;  // 0: a wait ran out
+};
+
+// The children words of stage d, [row][k']: score << 32 | token << kTagBits |
+// tag.  They live in the part of the stage's list buffer that no slice uses
+// (slices past kRoundSlicesMax), contiguous, so that a wave polls them with one
+// or two loads.
+__device__ __forceinline__ uint64_t* cand_words(const Plan& p, int d) {
+  return p.part_key + ((size_t)d * p.rows_max * kSlicesMax + kRoundSlicesMax) * p.kmax;
+}
+__device__ __forceinline__ int word_token(const Plan& p, uint64_t w) {
+  return min((int)((uint32_t)w >> kTagBits), p.V - 1);
+}
+__device__ __forceinline__ float word_value(uint64_t w) {
+  return __uint_as_float((uint32_t)(w >> 32));
+}
+
+// The plan as one stage uses it: its scalars are opaque to the compiler, so
+// that comparisons and addresses made from them are made anew in every stage.
+// Hoisted out of the stage loop they overflow the scalar registers, and the
+// reloads cost more than the few operations (0.6 us of a stage).
+// detach_plan() is called once before the loop: the launch arguments arrive in
+// blocks of 16 scalar registers, which are kept and spilled whole while any
+// field of theirs is in use.
+template <class T>
+__device__ __forceinline__ void opaque(T& x) {
+  asm volatile("" : "+s"(x));
+}
+// (a pointer stays known to address global memory: flat loads would also count
+// as LDS accesses in the waits for those)
+template <class T>
+__device__ __forceinline__ void opaque_global(T*& x) {
+  __attribute__((address_space(1))) T* g = (__attribute__((address_space(1))) T*)x;
+  opaque(g);
+  x = (T*)g;
+}
+__device__ __forceinline__ Plan stage_plan(const Plan& p) {
+  Plan q = p;
+  for (int* x : {&q.mode, &q.kk, &q.R, &q.G, &q.kk_inv, &q.rows_max, &q.kmax, &q.V, &q.r, &q.B,
+                 &q.merge_rows})
+    opaque(*x);
+  return q;
+}
+__device__ __forceinline__ Plan detach_plan(const Plan& p) {
+  Plan q = stage_plan(p);
+  opaque_global(q.L);
+  opaque_global(q.E);
+  opaque_global(q.Wt);
+  opaque_global(q.h);
+  opaque_global(q.part_key);
+  opaque_global(q.part_hd);
+  opaque(q.tag);
+  opaque(q.spin_ticks);
+  opaque(q.nchunk);
+  opaque(q.ntiles);
+  return q;
+}
+
+// x / k' for 0 <= x < 4096 (kk_inv = 65536 / k' + 1, k' <= 16).
+__device__ __forceinline__ int div_kk(const Plan& p, int x) { return (x * p.kk_inv) >> 16; }
+
+// A bounded wait: whether it may go on after its it-th miss.  The clock is
+// read at the first miss and every 16th (it costs as much as a poll).
+__device__ __forceinline__ bool wait_more(const Plan& p, int it, long long t0) {
+  if ((it & 15) == 0 && wall_clock64() - t0 > p.spin_ticks) return false;
+  __builtin_amdgcn_s_sleep(1);
+  return true;
+}
+
+// The wave waits until each lane's word carries the call's tag.
+__device__ __forceinline__ bool wait_word(const Plan& p, const uint64_t* src, uint64_t& w) {
+  const long long t0 = wall_clock64();
+  for (int it = 0;; ++it) {
+    w = load_agent(src);
+    if (__all(key_tagged(p, w))) return true;
+    if (!wait_more(p, it, t0)) return false;
+  }
+}
+
+// Sum over the T (2, 4 or 8) adjacent lanes of a group.
+__device__ __forceinline__ int group_sum(int v, int T) {
+  v += (int)perm<kXor1>((uint32_t)v);
+  if (T >= 4) v += (int)perm<kXor2>((uint32_t)v);
+  if (T >= 8) v += (int)perm<kHalfMirror>((uint32_t)v);
+  return v;
+}
+
+// Waits for the children words of stage d - 1 and ranks each request's layer:
+// the k' best become the head rows of stage d (fs.tok, fs.score).  All threads
+// of the workgroup; false if the wait ran out.  With 128 candidates or more
+// (one request, k' >= 12) only those at or above the lowest of the parents'
+// best children are ranked: each parent's children are sorted, so the k' best
+// of the layer are among them.
+__device__ __forceinline__ bool frontier(const Plan& p, int d, FrontShared& fs) {
+  int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  asm volatile("" : "+v"(tid));  // (nothing of this is kept over the stages)
+  const int lane = tid & 63;
+  const int kk = p.kk;
+  const int per_req = (d == 1 ? 1 : kk) * kk, n = p.R * per_req;
+  const bool prune = per_req >= 128;
+  uint64_t key = 0;
+  if (wave * 64 < n) {
+    const int c = min(tid, n - 1);
+    const int cp = div_kk(p, c);  // the candidate's parent (request-major)
+    const int pr = d == 1 ? 0 : cp - div_kk(p, cp) * kk;
+    const bool lead = tid < n && c == cp * kk;
+    uint64_t w;
+    if (!wait_word(p, cand_words(p, d - 1) + c, w) && lane == 0) fs.go = 0;
+    if (tid < n) {
+      key = node_key(word_value(w), d, word_token(p, w), pr);
+      if (!prune) fs.sk[tid] = key;
+      if (prune && lead) fs.first[pr] = (uint32_t)(key >> 32);
+    }
+  }
+  lds_barrier();
+  if (!fs.go) return false;
+  int total = n;
+  if (prune) {
+    uint32_t tf = fs.first[min(lane & 15, kk - 1)];
+    tf = min(tf, perm<kXor1>(tf));
+    tf = min(tf, perm<kXor2>(tf));
+    tf = min(tf, perm<kHalfMirror>(tf));
+    tf = min(tf, perm<kMirror>(tf));
+    const bool surv = tid < n && (uint32_t)(key >> 32) >= tf;
+    const uint64_t bal = __ballot(surv);
+    int base = 0;
+    if (lane == 0 && bal) base = atomicAdd(&fs.nsurv, __popcll(bal));
+    base = __builtin_amdgcn_readfirstlane(base);
+    if (surv) fs.sk[base + __popcll(bal & ((1ull << lane) - 1))] = key;
+    lds_barrier();
+    total = fs.nsurv;
+  }
+  // T lanes count each candidate's betters, at most 8 reads in turn each
+  // while the layer has 64 candidates (then all of a request's keys are read
+  // at fixed places, which takes half the instructions)
+  auto put = [&](uint64_t mine, int rq, int cnt) {
+    fs.tok[rq * kk + cnt] = min(0xFFFFF - (int)((mine >> 6) & 0xFFFFF), p.V - 1);
+    fs.score[rq * kk + cnt] = f32_unord((uint32_t)(mine >> 32));
+  };
+  if (n <= 64) {
+    const int e = min(tid >> 3, n - 1), q = tid & 7;
+    const uint64_t mine = fs.sk[e];
+    uint64_t o[8];
 #pragma unroll
-  for (int i = 0; i < (int)(sizeof(Plan) / 4); ++i)
-    ((int*)&p)[i] = __builtin_amdgcn_readfirstlane(((const int*)&lp)[i]);
-  return p;
+    for (int i = 0; i < 8; ++i) o[i] = fs.sk[q + 8 * i];
+    int rq = 0, s0 = 0, len = n;
+    if (p.R > 1) {
+      const int ep = div_kk(p, e);
+      rq = d == 1 ? ep : div_kk(p, ep);
+      s0 = rq * per_req;
+      len = per_req;
+    }
+    int cnt = 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) cnt += o[i] > mine && (uint32_t)(q + 8 * i - s0) < (uint32_t)len;
+    cnt = group_sum(cnt, 8);
+    if (q == 0 && cnt < kk && (tid >> 3) < n) put(mine, rq, cnt);
+    lds_barrier();
+    return true;
+  }
+  const int T = total <= 64 ? 8 : (total <= 128 ? 4 : 2);
+  const int e = tid / T;
+  const bool live = e < total;
+  const int ep = div_kk(p, e);
+  const int rq = p.R > 1 ? min(d == 1 ? ep : div_kk(p, ep), p.R - 1) : 0;
+  const uint64_t mine = fs.sk[min(e, total - 1)];
+  const uint64_t* keys = fs.sk + rq * per_req;
+  const int ncmp = prune ? total : per_req;
+  int cnt = 0;
+  for (int b = tid & (T - 1); b < ncmp; b += 8 * T) {
+    uint64_t o[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) o[i] = keys[min(b + i * T, ncmp - 1)];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) cnt += (b + i * T < ncmp) & (o[i] > mine);
+  }
+  cnt = group_sum(cnt, T);
+  if (live && (tid & (T - 1)) == 0 && cnt < kk) put(mine, rq, cnt);
+  lds_barrier();
+  if (prune && tid == 0) fs.nsurv = 0;
+  return true;
 }
 
-// The head-input code runs out of line with the plan read from an LDS copy:
-// its registers do not count against the W tiles the streaming loop keeps
-// resident.  The LDS objects are named directly (not passed), so that
-// accesses stay LDS ones.
-template <int DT>
-__device__ __noinline__ void frontier_call(const Plan& lp, int d) {
-  const Plan p = scalar_plan(lp);
-  compute_u<DT>(p, g_front, d, head_rows(p.mode, d, p.kk), (char*)g_dyn);
+// Shared-Markov: the next row's token is the greedy chain's, each request
+// row's best child of stage d - 1.
+__device__ __forceinline__ bool chain_front(const Plan& p, int d, FrontShared& fs) {
+  if (threadIdx.x < 64) {
+    const int rq = min((int)threadIdx.x, p.R - 1);
+    uint64_t w;
+    if (!wait_word(p, cand_words(p, d - 1) + rq * p.kk, w) && threadIdx.x == 0) fs.go = 0;
+    fs.tok[rq] = word_token(p, w);
+  }
+  lds_barrier();
+  return fs.go != 0;
 }
 
-// Blocks [0, G) stream one V-slice each; block G is the keeper.  A streaming
-// block publishes the stage-d partial of its slice as tagged words (no
-// ordering, no flag) and, for stage d+1, waits for the frontier words that
-// the keeper publishes.  The keeper waits for all slice partials of stage d
-// (re-reading the records that are not complete yet), merges them, selects
-// the stage-(d+1) frontier and publishes it first; then it keeps the pool,
-// the trace and the running top-N (in LDS), and emits the tree after the last
-// stage.  All cross-workgroup words are written and read with agent-coherent
-// (L2-bypassing) accesses; each word is valid on its own, so no fence is
-// needed anywhere.  The tagged buffers are cleared before every call.
-template <int DT, int NCMAX, int KMAX, bool FOLD>
-__global__ __launch_bounds__(kRoundWaves * 64) void round_kernel(Plan p) {
-  __shared__ int sh_go;
-  SelShared& ssh = g_sel;
-  char* dyn = (char*)g_dyn;
-  if (blockIdx.x < p.G) {
-    __shared__ HeadShared<KMAX, kRoundWaves> hsh;
-    FrontShared& fs = g_front;
-    __shared__ Plan sp;  // read by the out-of-line stage code
-    if (threadIdx.x == 0) sp = p;
-    u32x4* wl = (u32x4*)(dyn + p.lds_tile_offset);
-    if constexpr (FOLD)
-      stream_block_fold<DT, NCMAX, KMAX>(p, sp, hsh, fs, dyn, wl, sh_go);
-    else
-      stream_block<DT, NCMAX, KMAX>(p, sp, hsh, fs, dyn, wl, sh_go);
-    return;
+// The keys of the wave's logits at or above thr (v[i] of lane l is token tok0 +
+// i * step), compacted into cb, then `extra` (one per lane < nextra), then
+// eight zeros.  Returns their count, or -1 if more than
+// kCandCap logits pass.
+constexpr int kCandCap = 64;
+__device__ __forceinline__ int row_cands(const float (&v)[kZPer], float thr, int tok0, int step,
+                                         uint64_t* cb, uint64_t extra, int nextra) {
+  const int lane = threadIdx.x & 63;
+  int n = 0;
+#pragma unroll
+  for (int i = 0; i < kZPer; ++i) {
+    const bool c = v[i] >= thr;
+    const uint64_t m = __ballot(c);
+    if (m) {
+      const int pos = n + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                         __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+      if (c && pos < kCandCap) cb[pos] = child_key(v[i], tok0 + i * step);
+      n += __popcll(m);
+    }
+  }
+  if (n > kCandCap) return -1;
+  if (lane < nextra) cb[n + lane] = extra;
+  n += nextra;
+  if (lane < 8) cb[n + lane] = 0;
+  __builtin_amdgcn_wave_barrier();
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  return n;
+}
+
+// How many of cb[0..n) (followed by eight zeros) exceed key.
+__device__ __forceinline__ int cand_rank(const uint64_t* cb, int n, uint64_t key) {
+  int cnt = 0;
+  int c = 0;
+  do {
+    uint64_t o[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) o[i] = cb[c + i];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) cnt += o[i] > key;
+    c += 8;
+  } while (c < n);
+  return cnt;
+}
+
+// LDS of a streaming workgroup's row phase: each wave's candidates, and what
+// its rows' earlier batches left.
+struct RowShared {
+  __attribute__((aligned(16))) uint64_t cb[kRoundWaves][kCandCap + kNarrowRows + 8];
+  uint64_t carry[kNarrowRows][kNarrowRows];  // (slices of several batches)
+  float2 cms[kNarrowRows];
+};
+
+// One streaming workgroup: a fixed V-slice whose W stays on chip, and B stages
+// of frontier, head input, matrix product and the rows' records.  The logits
+// go through LDS once, so that one wave then holds a whole row of the slice
+// (10 logits per lane): its maximum and sum of exp are wave-wide reductions,
+// and its best keys are the few at or above a threshold that the lanes' maxima
+// give (the third largest of eight lane groups' maxima for the record, the
+// least of the groups' for the list), ranked by counting.  Per-lane lists
+// merged over lanes and waves took 3.6 us of a stage, k' pops of the wave-wide
+// maximum 4.2 us.  Slices of more than kZTiles tiles go in batches, the k' best
+// of the earlier ones carried along in the first k' lanes.
+template <int DT, int NCMAX, bool R8>
+__device__ __forceinline__ void stream_block(const Plan& pl, FrontShared& fs, RowShared& rsh,
+                                             char* dyn) {
+  const Plan p0 = detach_plan(pl);
+  constexpr int RT = resident_reg_tiles(NCMAX);
+  constexpr int ROWS = round_rows(R8), RPW = ROWS / kRoundWaves;
+  constexpr int US = u_stride(NCMAX);
+  constexpr int KC = DT ? 32 : 16;   // rank elements per chunk
+  constexpr int ESZ = DT ? 2 : 4;
+  constexpr int Q = DT ? 4 : 1;      // head-input elements per work item
+  constexpr int NTH = kRoundWaves * 64;
+  constexpr int MAXQ = (ROWS * NCMAX * KC / Q + NTH - 1) / NTH;  // items per thread
+  char* ul = dyn;
+  float* zb = (float*)(dyn + ROWS * US);
+  u32x4* wl = (u32x4*)(dyn + round_tile_offset(NCMAX, R8));
+  const int tid = threadIdx.x, lane0 = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g = blockIdx.x, G = p0.G;
+  const int nt0 = (p0.ntiles - g + G - 1) / G;  // tiles of the slice
+  const int nlds0 = min(max(nt0 - RT * kRoundWaves, 0), p0.lds_tiles);
+  // tokens of the slice (only the vocabulary's last tile is partial)
+  const int nvalid0 =
+      nt0 * kTile - (g + G * (nt0 - 1) == p0.ntiles - 1 ? p0.ntiles * kTile - p0.V : 0);
+  const int nbatch0 = (nt0 + kZTiles - 1) / kZTiles;
+
+  // the roots' head input first: its loads go out before the W stream's
+  for (int i = tid; i < ROWS * US / 16; i += NTH) ((u32x4*)ul)[i] = u32x4{0u, 0u, 0u, 0u};
+  if (tid < p0.R) {
+    const int root = p0.root[tid];
+    fs.tok[tid] = root < 0 || root >= p0.V ? 0 : root;
+  }
+  lds_barrier();
+  // the thread's head-input items: row << 16 | element, -1 past the rows
+  int item[MAXQ];
+#pragma unroll
+  for (int q = 0; q < MAXQ; ++q) {
+    const int e = (q * NTH + tid) * Q, row = e / p0.r;
+    item[q] = row << 16 | (e - row * p0.r);
+  }
+  typedef uint32_t evec __attribute__((ext_vector_type(DT ? 2 : 1)));
+  typedef float hvec __attribute__((ext_vector_type(Q)));
+  hvec hv[MAXQ];
+  evec ev[MAXQ];
+  // loads for the head input of stage d's rows (fs.tok), and the rest of it
+  auto load_u = [&](const Plan& p, int d, int P, int rows) __attribute__((always_inline)) {
+#pragma unroll
+    for (int q = 0; q < MAXQ; ++q) {
+      int it = item[q];
+      asm volatile("" : "+v"(it));  // (addresses are not kept over the stages)
+      const int row = it >> 16, j = it & 0xffff;
+      if (row < rows) {
+        ev[q] = *(const evec*)((const char*)p.E + (uint32_t)((fs.tok[row] * p.r + j) * ESZ));
+        const int req = P == 1 ? row : div_kk(p, row);
+        hv[q] = *(const hvec*)(p.h + ((size_t)req * p.B + d) * p.r + j);
+      }
+    }
+  };
+  auto finish_u = [&](int rows) __attribute__((always_inline)) {
+#pragma unroll
+    for (int q = 0; q < MAXQ; ++q) {
+      int it = item[q];
+      asm volatile("" : "+v"(it));  // (addresses are not kept over the stages)
+      const int row = it >> 16, j = it & 0xffff;
+      if (row >= rows) continue;
+      char* dst = ul + row * US + j * ESZ;
+      if constexpr (DT) {
+        float y[4];
+        uint32_t bad = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          bool ok;
+          y[i] = silu_fast(__uint_as_float((i & 1) ? ev[q][i / 2] & 0xffff0000u : ev[q][i / 2] << 16),
+                           hv[q][i], ok);
+          bad |= ok ? 0u : 1u << i;
+        }
+        if (__builtin_expect(__any(bad), 0)) {
+#pragma unroll 1
+          for (int i = 0; i < 4; ++i) {
+            if (!__any(bad >> i & 1)) continue;
+            const uint32_t ew = i & 2 ? ev[q][1] : ev[q][0];
+            const float h = i & 2 ? (i & 1 ? hv[q][3] : hv[q][2]) : (i & 1 ? hv[q][1] : hv[q][0]);
+            const float x = silu_f32_tab(__uint_as_float((i & 1) ? ew & 0xffff0000u : ew << 16), h,
+                                         fs.tab);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) y[k] = k == i && (bad >> i & 1) ? x : y[k];
+          }
+        }
+        u32x2 w;
+        w[0] = (uint32_t)bf16_rne(y[0]) | ((uint32_t)bf16_rne(y[1]) << 16);
+        w[1] = (uint32_t)bf16_rne(y[2]) | ((uint32_t)bf16_rne(y[3]) << 16);
+        *(u32x2*)dst = w;
+      } else {
+        *(float*)dst = silu_f32_tab(__uint_as_float(ev[q][0]), hv[q][0], fs.tab);
+      }
+    }
+  };
+  if (p0.mode != 2) load_u(p0, 0, 1, p0.R);
+
+  // the resident W tiles: the wave's tile i is the slice's tile wave + 8 i;
+  // A fragment rows are its 16 tokens (chunks past the rank re-read the last
+  // one and meet zero head input)
+  const int nchunk = p0.nchunk;
+  auto wsrc = [&](int j, int ln) __attribute__((always_inline)) {
+    const int tok = min((g + G * min(j, nt0 - 1)) * kTile + (ln & 15), p0.V - 1);
+    return (const char*)p0.Wt + ((size_t)tok * p0.r + (ln >> 4) * (KC / 4)) * ESZ;
+  };
+  u32x4 areg[RT][NCMAX];
+  if (p0.mode != 2) {
+    for (int li = wave; li < nlds0; li += kRoundWaves) {
+      const char* src = wsrc(RT * kRoundWaves + li, lane0);
+#pragma unroll
+      for (int c = 0; c < NCMAX; ++c)
+        load_lds16(src + (size_t)min(c, nchunk - 1) * KC * ESZ, wl + ((size_t)li * NCMAX + c) * 64);
+    }
+#pragma unroll
+    for (int i = 0; i < RT; ++i) {
+      const char* src = wsrc(wave + kRoundWaves * i, lane0);
+#pragma unroll
+      for (int c = 0; c < NCMAX; ++c)
+        areg[i][c] = *(const u32x4*)(src + (size_t)min(c, nchunk - 1) * KC * ESZ);
+    }
   }
 
-  // the keeper
-  __shared__ int s_front_node[kNarrowRows], s_front_tok[kNarrowRows];
-  __shared__ float s_front_score[kNarrowRows];
-  uint64_t* s_top = (uint64_t*)(dyn + p.lds_top_offset);
-  const State st{s_front_node, s_front_tok, s_front_score, s_top,
-                 (int*)(s_top + (size_t)p.R * p.N), 0};
-  constexpr bool kInline = KMAX > 8;  // keeps the launch arguments out of scratch
-  for (int req = 0; req < p.R; ++req) {
-    if constexpr (kInline)
-      init_request_body(p, req, threadIdx.x, blockDim.x);
-    else
-      init_request(p, req, threadIdx.x, blockDim.x);
+  for (int d = 0; d < p0.B; ++d) {
+    const Plan p = stage_plan(p0);
+    const int kk = p.kk, G = p.G;
+    const int P = head_rows(p.mode, d, kk), rows = p.R * P;
+    // (the lane's addresses are derived anew in every stage: kept over the
+    // stages they would take the registers of a W tile)
+    int lane = lane0;
+    asm volatile("" : "+v"(lane));
+    const int col = lane & 15, grp = lane >> 4;
+    const int tok0 = (g + G * grp) * kTile + col;  // the lane's first token
+    const int step = 4 * G * kTile;                // its next one
+    const char* ub = ul + (R8 ? col & 7 : col) * US + grp * 16;
+    float* zw = zb + col * kZStride + grp * 4;
+    const bool zcol = !R8 || col < 8;
+    // L_d of the lane's tokens (first batch) for the wave's first row, in
+    // flight during the wait; its second row is mostly of the same request
+    uint32_t lraw[kZPer];
+    auto load_l = [&](int b, int row) __attribute__((always_inline)) {
+      const int req = P == 1 ? row : div_kk(p, row);
+      const char* lrow = (const char*)p.L + ((size_t)req * p.B + d) * p.V * ESZ;
+      // (opaque, so that the offsets are recomputed rather than kept over the stages)
+      int t = tok0 + b * kZPer * step;
+      asm volatile("" : "+v"(t));
+#pragma unroll
+      for (int i = 0; i < kZPer; ++i)
+        lraw[i] = load_raw<DT>(lrow + (uint32_t)min(t + i * step, p.V - 1) * ESZ, 0);
+    };
+    const int row0 = min(wave * RPW, rows - 1);
+    load_l(0, row0);
+    TIMELINE_SLICE(d, 0);
+    if (p.mode != 2) {
+      if (d > 0) {
+        if (!(p.mode == 0 ? frontier(p, d, fs) : chain_front(p, d, fs))) return;
+        load_u(p, d, P, rows);
+      }
+      finish_u(rows);
+      lds_barrier();
+    }
+    TIMELINE_SLICE(d, 1);
+    if (d == 0) {
+      wait_vmcnt<0>();  // the LDS tiles (each wave reads only its own)
+      __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    }
+
+    for (int b = 0; b < nbatch0; ++b) {
+      const Plan ps = p;
+      const int lane_s = lane;
+      const Plan p = stage_plan(ps);
+      const int kk = p.kk;
+      int nt = nt0, nlds = nlds0, nbatch = nbatch0, nvalid = nvalid0, lane = lane_s;
+      for (int* x : {&nt, &nlds, &nbatch, &nvalid}) opaque(*x);
+      asm volatile("" : "+v"(lane));
+      if (b > 0) {
+        load_l(b, row0);
+        lds_barrier();  // the earlier batch's logits are read
+      }
+      if (p.mode != 2) {
+        if (b == 0) {
+          // the register tiles and the wave's first LDS tile side by side, the
+          // next chunks' LDS reads in flight while this group multiplies
+          auto resident = [&](auto with_lds, auto tiles) __attribute__((always_inline)) {
+            constexpr bool WL = decltype(with_lds)::value;
+            constexpr int RT = decltype(tiles)::value;
+            constexpr int BG = 2, NG = NCMAX / BG;
+            const u32x4* a = wl + (size_t)wave * NCMAX * 64 + lane;
+            f32x4 acc[RT + 1];
+#pragma unroll
+            for (int i = 0; i <= RT; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+            u32x4 bq[2][BG], aq[2][BG];
+#pragma unroll
+            for (int e = 0; e < BG; ++e) {
+              bq[0][e] = *(const u32x4*)(ub + e * 64);
+              if (WL) aq[0][e] = a[e * 64];
+            }
+#pragma unroll
+            for (int gq = 0; gq < NG; ++gq) {
+              if (gq + 1 < NG) {
+#pragma unroll
+                for (int e = 0; e < BG; ++e) {
+                  bq[(gq + 1) & 1][e] = *(const u32x4*)(ub + ((gq + 1) * BG + e) * 64);
+                  if (WL) aq[(gq + 1) & 1][e] = a[((gq + 1) * BG + e) * 64];
+                }
+              }
+              __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+              for (int e = 0; e < BG; ++e) {
+#pragma unroll
+                for (int i = 0; i < RT; ++i)
+                  acc[i] = mfma_chunk<DT>(areg[i][gq * BG + e], bq[gq & 1][e], acc[i]);
+                if (WL) acc[RT] = mfma_chunk<DT>(aq[gq & 1][e], bq[gq & 1][e], acc[RT]);
+              }
+              __builtin_amdgcn_sched_barrier(0);
+            }
+            if (zcol) {
+#pragma unroll
+              for (int i = 0; i < RT + (WL ? 1 : 0); ++i)
+                *(f32x4*)(zw + (wave + kRoundWaves * i) * kTile) = acc[i];
+            }
+          };
+          if (nt <= kRoundWaves)  // (small vocabularies)
+            resident(std::false_type{}, std::integral_constant<int, 1>{});
+          else if (RT < kBatchTiles && wave < nlds)
+            resident(std::true_type{}, std::integral_constant<int, RT>{});
+          else
+            resident(std::false_type{}, std::integral_constant<int, RT>{});
+        }
+        const int i0 = b > 0 ? b * kBatchTiles : RT + (RT < kBatchTiles && wave < nlds ? 1 : 0);
+        for (int i = i0; i < (b + 1) * kBatchTiles; ++i) {
+          const int j = wave + kRoundWaves * i, li = j - RT * kRoundWaves;
+          if (j >= nt) break;
+          f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+          auto tile = [&](auto load) __attribute__((always_inline)) {
+            constexpr int BG = NCMAX < 4 ? NCMAX : 4, NG = NCMAX / BG;
+            u32x4 aq[2][BG];
+#pragma unroll
+            for (int e = 0; e < BG; ++e) aq[0][e] = load(e);
+#pragma unroll
+            for (int gq = 0; gq < NG; ++gq) {
+              if (gq + 1 < NG) {
+#pragma unroll
+                for (int e = 0; e < BG; ++e) aq[(gq + 1) & 1][e] = load((gq + 1) * BG + e);
+              }
+              __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+              for (int e = 0; e < BG; ++e)
+                acc = mfma_chunk<DT>(aq[gq & 1][e], *(const u32x4*)(ub + (gq * BG + e) * 64), acc);
+              __builtin_amdgcn_sched_barrier(0);
+            }
+          };
+          if (li < nlds) {
+            const u32x4* a = wl + (size_t)li * NCMAX * 64 + lane;
+            tile([&](int c) { return a[c * 64]; });
+          } else {
+            const char* src = wsrc(j, lane);
+            tile([&](int c) { return *(const u32x4*)(src + (size_t)min(c, nchunk - 1) * KC * ESZ); });
+          }
+          if (zcol) *(f32x4*)(zw + (j - b * kZTiles) * kTile) = acc;
+        }
+        lds_barrier();
+      }
+      if (b == 0) TIMELINE_SLICE(d, 2);
+      const bool last = b + 1 == nbatch;
+#pragma unroll 1
+      for (int rr = 0; rr < RPW; ++rr) {
+        const int row = wave * RPW + rr;
+        if (row >= rows) break;
+        // an earlier batch's best keys (by lane) and (max, sum of exp)
+        const uint64_t carried = b > 0 && lane < kNarrowRows ? rsh.carry[row][lane] : 0;
+        const float2 ms = b > 0 ? rsh.cms[row] : make_float2(-INFINITY, 0.0f);
+        uint64_t lkey = 0;
+        if (rr > 0 && (b > 0 || (P == 1 ? p.R > 1 : div_kk(p, row) != div_kk(p, row0)))) load_l(b, row);
+        float v[kZPer];
+        const int left = nvalid - b * kZTiles * kTile - lane;
+#pragma unroll
+        for (int i = 0; i < kZPer; ++i) {
+          const float z = p.mode == 2 ? 0.0f : zb[row * kZStride + i * 64 + lane];
+          v[i] = i * 64 < left ? z + raw_to_f32<DT>(lraw[i]) : -INFINITY;
+        }
+        // the lane's two best, its group's best (8 lanes; as ordered integers,
+        // whose permutes fold into the maximum), the row's maximum and the
+        // third largest group
+        float lm = v[0], lm2 = -INFINITY;
+#pragma unroll
+        for (int i = 1; i < kZPer; ++i) {
+          lm2 = fmaxf(lm2, fminf(lm, v[i]));
+          lm = fmaxf(lm, v[i]);
+        }
+        const uint32_t o1 = f32_ord(lm);
+        uint32_t g4 = max(o1, perm<kXor1>(o1));
+        g4 = max(g4, perm<kXor2>(g4));
+        const uint32_t g8 = max(g4, perm<kHalfMirror>(g4));
+        const uint32_t om = all_max<3>(g8);
+        float M = f32_unord(__builtin_amdgcn_readfirstlane(om));
+        uint32_t gt = g8 == om ? 0u : g8;
+        const uint32_t om2 = all_max<3>(gt);
+        gt = gt == om2 ? 0u : gt;
+        const uint32_t om3 = all_max<3>(gt);
+        // (0 when fewer groups hold a logit, or they tie: all logits pass)
+        const float t3 = om3 <= f32_ord(-FLT_MAX) ? -FLT_MAX : f32_unord(om3);
+        if (b > 0) M = fmaxf(M, ms.x);
+        float s = 0.0f;
+#pragma unroll
+        for (int i = 0; i < kZPer; ++i) s += exp2_raw((v[i] - M) * kLog2e);
+        s = all_sum(s);
+        if (b > 0) s += ms.y * exp2_raw((ms.x - M) * kLog2e);
+        int tb = tok0 + b * kZPer * step;
+        asm volatile("" : "+v"(tb));  // (as for the L_d offsets)
+        uint64_t* cb = rsh.cb[wave];
+        uint64_t* rec = slice_record(p, d, row) + g;
+        uint64_t* list = p.part_key + (((size_t)d * p.rows_max + row) * kSlicesMax + g) * p.kmax;
+        auto put = [&](uint64_t* at, uint64_t w) __attribute__((always_inline)) {
+          __hip_atomic_store(at, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        };
+        const uint64_t sumw = ((uint64_t)p.tag << 32) | __float_as_uint(s);
+        bool slow = false;
+        if (nbatch == 1) {
+          // the record: the keys at or above t3, mostly one per lane
+          const bool c = lm >= t3;
+          const uint64_t cm = __ballot(c);
+          int n = __popcll(cm);
+          if (n <= 8 && !__any(lm2 >= t3)) {
+            int li = kZPer - 1;
+#pragma unroll
+            for (int i = kZPer - 2; i >= 0; --i) li = v[i] == lm ? i : li;
+            const int pos = (int)__builtin_amdgcn_mbcnt_hi(
+                (uint32_t)(cm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)cm, 0));
+            const uint64_t key = child_key(lm, tb + li * step);
+            if (lane < 8) cb[lane] = 0;
+            __builtin_amdgcn_wave_barrier();
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
+            if (c) cb[pos] = key;
+            __builtin_amdgcn_wave_barrier();
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
+            const int rank = cand_rank(cb, 1, key);
+            if (c && rank < kHeadKeys) put(rec + rank * kSlicesMax, key | p.tag);
+          } else {
+            n = row_cands(v, t3, tb, step, cb, 0, 0);
+            slow = n < 0;
+            for (int e = lane; e < n; e += 64) {
+              const uint64_t key = cb[e];
+              const int rank = cand_rank(cb, n, key);
+              if (rank < kHeadKeys) put(rec + rank * kSlicesMax, key | p.tag);
+            }
+          }
+          if (!slow) {
+            if (lane >= n && lane < kHeadKeys) put(rec + lane * kSlicesMax, p.tag);
+            if (lane == 63) put(rec + kHeadKeys * kSlicesMax, sumw);
+          }
+        }
+        if (!slow && (nbatch > 1 || kk > kHeadKeys)) {
+          // the list, off the critical path
+          // (the least group's best has at least k' keys at or above it; a few
+          // bisections towards the row's maximum leave few more)
+          uint32_t gm = ~(kk > 8 ? g4 : g8);
+          if (kk > 8) gm = max(gm, perm<kHalfMirror>(gm));
+          gm = max(gm, perm<kMirror>(gm));
+          auto mx = [](uint32_t x, uint32_t y) { return max(x, y); };
+          gm = ~swap_op<32>(swap_op<16>(gm, mx), mx);
+          uint32_t lo = __builtin_amdgcn_readfirstlane(gm);
+          uint32_t hi = __builtin_amdgcn_readfirstlane(om);
+#pragma unroll 1
+          for (int it = 0; it < 12 && lo < hi; ++it) {
+            const uint32_t mid = lo + (hi - lo + 1) / 2;
+            const int c = __popcll(__ballot(o1 >= mid));
+            if (c < kk) {
+              hi = mid - 1;
+            } else {
+              lo = mid;
+              if (c < 2 * kk) break;
+            }
+          }
+          const float tl = lo <= f32_ord(-FLT_MAX) ? -FLT_MAX : f32_unord(lo);
+          const int n = row_cands(v, tl, tb, step, cb, carried, b > 0 ? kk : 0);
+          slow = n < 0;
+          if (!slow) {
+            uint64_t keys[2];
+            int rank[2];
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+              const int e = lane + 64 * q;
+              keys[q] = e < n ? cb[e] : 0;
+              rank[q] = e < n ? cand_rank(cb, n, keys[q]) : kNarrowRows;
+            }
+            if (nbatch == 1) {
+#pragma unroll
+              for (int q = 0; q < 2; ++q)
+                if (rank[q] < p.kmax) put(list + rank[q], keys[q] | p.tag);
+              if (lane >= n && lane < p.kmax) put(list + lane, p.tag);
+            } else {
+              __builtin_amdgcn_wave_barrier();
+              __atomic_signal_fence(__ATOMIC_SEQ_CST);
+              if (lane < kNarrowRows) cb[lane] = 0;
+              __builtin_amdgcn_wave_barrier();
+              __atomic_signal_fence(__ATOMIC_SEQ_CST);
+#pragma unroll
+              for (int q = 0; q < 2; ++q)
+                if (rank[q] < kk) cb[rank[q]] = keys[q];
+              __builtin_amdgcn_wave_barrier();
+              __atomic_signal_fence(__ATOMIC_SEQ_CST);
+              lkey = lane < kk ? cb[lane] : 0;
+            }
+          }
+        }
+        if (slow) {
+          // many equal logits: the best key below the last one, over and over
+          const int req = P == 1 ? row : div_kk(p, row);
+      const char* lrow = (const char*)p.L + ((size_t)req * p.B + d) * p.V * ESZ;
+          uint64_t prev = ~0ull;
+          for (int it = 0; it < max(kk, kHeadKeys); ++it) {
+            uint64_t top = carried < prev ? carried : 0;
+#pragma unroll 1
+            for (int i = 0; i < kZPer && i * 64 < left; ++i) {
+              const float z = p.mode == 2 ? 0.0f : zb[row * kZStride + i * 64 + lane];
+              const int tok = tb + i * step;
+              const uint64_t key =
+                  child_key(z + raw_to_f32<DT>(load_raw<DT>(lrow, (size_t)tok)), tok);
+              top = key < prev && key > top ? key : top;
+            }
+            prev = wave_max_u64(top);
+            if (lane == it) lkey = prev;
+          }
+        }
+        if (last && (slow || nbatch > 1)) {
+          if (lane < kRecWords) put(rec + lane * kSlicesMax, lane < kHeadKeys ? lkey | p.tag : sumw);
+          if (kk > kHeadKeys && lane < p.kmax) put(list + lane, lkey | p.tag);
+        }
+        if (!last) {
+          if (lane < kNarrowRows) rsh.carry[row][lane] = lkey;
+          if (lane == 0) rsh.cms[row] = make_float2(M, s);
+        }
+      }
+    }
+    TIMELINE_SLICE(d, 3);
   }
-  for (int i = threadIdx.x; i < p.R * p.kk; i += blockDim.x) {
-    const int r0 = p.root[i / p.kk];
-    st.front_node[i] = 0;
-    st.front_tok[i] = r0 < 0 || r0 >= p.V ? 0 : r0;
-    st.front_score[i] = 0.0f;
+}
+
+constexpr int kMergeKeys = kRoundSlicesMax * kHeadKeys;  // record keys of a row
+struct MergeShared {
+  __attribute__((aligned(16))) uint64_t cand[2][kMergeKeys + 8];
+  __attribute__((aligned(16))) uint32_t gmax[2][32];  // best key (high word) of each slice group
+  float2 wms[2][2][4];  // [stage parity][row][wave]: (max, sum of exp)
+  __attribute__((aligned(16))) u32x4 sink[2][64];  // (where prefetched rows land)
+  int n[2];
+  int go;
+};
+
+// A merger workgroup: the k' children and the lse of rpm (1 or 2) rows of
+// every stage, four waves per row, one slice per lane.  The row's k' best lie
+// among the record keys at or above the k'-th largest of the slice groups'
+// best keys (those are k' distinct keys), a handful, which are ranked by
+// counting: against k' pops of the wave-wide maximum over four slices per lane
+// this took 0.6 us instead of 1.9 us.  Only if a slice gave up all of its
+// record keys, its full list (and those of the other slices that gave a key)
+// settles the row.
+__device__ __forceinline__ void merge_block(const Plan& pl, FrontShared& fs, MergeShared& ms, int m) {
+  const Plan p0 = detach_plan(pl);
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lrow = wave >> 2, q = wave & 3;
+  if (tid == 0) {
+    ms.n[0] = ms.n[1] = 0;
+    ms.go = 1;
   }
-  for (int req = threadIdx.x; req < p.R; req += blockDim.x) {
+  if (tid < 64) ms.gmax[tid >> 5][tid & 31] = 0;
+  lds_barrier();
+  for (int d = 0; d < p0.B; ++d) {
+    const Plan p = stage_plan(p0);
+    int lane = tid & 63;
+    asm volatile("" : "+v"(lane));
+    const int sl = q * 64 + lane;
+    const int G = p.G, kk = p.kk, row = m * p.merge_rows + lrow;
+    const bool live = sl < G;
+    // 16 or 32 groups of adjacent slices, more than k' of them where G allows
+    const bool wide_groups = kk <= 8 && G > 128;
+    const int gsh = wide_groups ? 4 : (G <= 64 ? 1 : (G <= 128 ? 2 : 3));
+    const int rows = p.R * head_rows(p.mode, d, kk);
+    if (p.mode == 0 && d > 0 && !frontier(p, d, fs)) return;  // the parents' scores
+    const bool act = lrow < p.merge_rows && row < rows;
+    uint64_t k[kHeadKeys] = {0, 0, 0};
+    if (act && q * 64 < G) {
+      const uint64_t* rec = slice_record(p, d, row) + sl;
+      float s = 0.0f;
+      bool have = !live;
+      const long long t0 = wall_clock64();
+      for (int it = 0;; ++it) {
+        if (!have) {
+          uint64_t w[kRecWords];
+#pragma unroll
+          for (int i = 0; i < kRecWords; ++i) w[i] = load_agent(rec + i * kSlicesMax);
+          have = sum_tagged(p, w[kHeadKeys]);
+#pragma unroll
+          for (int i = 0; i < kHeadKeys; ++i) {
+            have = have && key_tagged(p, w[i]);
+            k[i] = w[i];
+          }
+          s = __uint_as_float((uint32_t)w[kHeadKeys]);
+        }
+        if (__all(have)) break;
+        if (!wait_more(p, it, t0)) {
+          if (lane == 0) ms.go = 0;
+          break;
+        }
+      }
+      // (the tag's bits then hold the key's place in its record)
+#pragma unroll
+      for (int i = 0; i < kHeadKeys; ++i)
+        k[i] = live && (k[i] >> kTagBits) != 0 ? ((k[i] >> kTagBits) << kTagBits) | i : 0;
+      const float mv = live ? child_key_value(k[0]) : kNegBig;
+      uint32_t hi = (uint32_t)(k[0] >> 30);
+      hi = max(hi, perm<kXor1>(hi));
+      if (gsh >= 2) hi = max(hi, perm<kXor2>(hi));
+      if (gsh >= 3) hi = max(hi, perm<kHalfMirror>(hi));
+      if (gsh >= 4) hi = max(hi, perm<kMirror>(hi));
+      const float M = f32_unord(all_max<0>(f32_ord(mv)));
+      const float S = all_sum(live ? s * exp2_raw((mv - M) * kLog2e) : 0.0f);
+      if (lane == 0) ms.wms[d & 1][lrow][q] = make_float2(M, S);
+      if ((lane & ((1 << gsh) - 1)) == 0) ms.gmax[lrow][sl >> gsh] = hi;
+    }
+    lds_barrier();
+    if (!ms.go) return;
+    if (act && q * 64 < G) {
+      const uint32_t x = ms.gmax[lrow][lane & 31];
+      int cnt = 0;
+      const int ng = wide_groups ? 16 : 32;
+      for (int i = 0; i < ng; i += 16) {
+        u32x4 o[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o[j] = *(const u32x4*)&ms.gmax[lrow][i + 4 * j];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) cnt += o[j / 4][j & 3] > x;
+      }
+      // the k'-th largest group maximum: the least with fewer than k' above it
+      const uint32_t thr = ~all_max<0>((lane & 31) < ng && cnt < kk ? ~x : 0u);
+      int pos = 0;
+      uint64_t bal[kHeadKeys];
+      bool c[kHeadKeys];
+#pragma unroll
+      for (int i = 0; i < kHeadKeys; ++i) {
+        c[i] = k[i] != 0 && (uint32_t)(k[i] >> 30) >= thr;
+        bal[i] = __ballot(c[i]);
+        pos += __popcll(bal[i]);
+      }
+      if (lane == 0 && pos) pos = atomicAdd(&ms.n[lrow], pos);
+      pos = __builtin_amdgcn_readfirstlane(pos);
+#pragma unroll
+      for (int i = 0; i < kHeadKeys; ++i) {
+        if (c[i]) ms.cand[lrow][pos + __popcll(bal[i] & ((1ull << lane) - 1))] = k[i];
+        pos += __popcll(bal[i]);
+      }
+    }
+    lds_barrier();
+    if (!act || q != 0) continue;
+    const int n = ms.n[lrow];
+    if (lane == 0) ms.n[lrow] = 0;
+    uint64_t* cand = ms.cand[lrow];
+    if (lane < 8) cand[n + lane] = 0;  // (cand_rank reads eight at a time)
+    __builtin_amdgcn_wave_barrier();
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    // the lse over the waves' slices (lane i: wave i & 3)
+    const float2 wm = (lane & 3) * 64 < G ? ms.wms[d & 1][lrow][lane & 3]
+                                          : make_float2(kNegBig, 0.0f);
+    float M = fmaxf(wm.x, permf<kXor1>(wm.x));
+    M = fmaxf(M, permf<kXor2>(M));
+    float S = wm.y * exp2_raw((wm.x - M) * kLog2e);
+    S += permf<kXor1>(S);
+    S += permf<kXor2>(S);
+    const float lse = M + logf(S);
+    const float parent = p.mode == 0 && d > 0 ? fs.score[row] : 0.0f;
+    uint64_t* out = cand_words(p, d) + row * kk;
+    auto publish = [&](int rank, uint64_t key) __attribute__((always_inline)) {
+      const float lp = child_key_value(key) - lse;
+      const float score = p.mode == 0 ? parent + lp : lp;
+      const int tok = min(max(child_key_token(key), 0), p.V - 1);
+      __hip_atomic_store(out + rank,
+                         ((uint64_t)__float_as_uint(score) << 32) | ((uint64_t)tok << kTagBits) |
+                             p.tag,
+                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    // a slice all of whose record keys are among the k' best may hold more
+    bool more = false;
+    int r0 = kk;
+    uint64_t key0 = 0;
+    if (lane < n) {
+      key0 = cand[lane];
+      r0 = cand_rank(cand, n, key0);
+      more = r0 < kk && (int)(key0 & kTagMask) == kHeadKeys - 1;
+    }
+    for (int e = lane + 64; e < n; e += 64) {  // (many ties at the threshold)
+      const uint64_t key = cand[e];
+      more = more || ((int)(key & kTagMask) == kHeadKeys - 1 && cand_rank(cand, n, key) < kk);
+    }
+    if (kk <= kHeadKeys || !__any(more)) {
+      if (r0 < kk) publish(r0, key0);
+      for (int e = lane + 64; e < n; e += 64) {
+        const uint64_t key = cand[e];
+        const int rank = cand_rank(cand, n, key);
+        if (rank < kk) publish(rank, key);
+      }
+      if (p.mode == 0 && d + 1 < p.B) {
+        // the children's embedding rows into the memory-side cache: the
+        // streaming workgroups read the chosen ones as soon as they have
+        // ranked the words
+        uint64_t b = __ballot(r0 < kk);
+        const int ru = p.r * (p.dtype ? 2 : 4) / 16;
+        while (b) {
+          const int src = __builtin_ctzll(b);
+          b &= b - 1;
+          const int tok = min(max(child_key_token(readlane_u64(key0, src)), 0), p.V - 1);
+          if (lane < ru) load_lds16((const char*)p.E + ((size_t)tok * ru + lane) * 16, ms.sink[lrow]);
+        }
+      }
+      continue;
+    }
+    // The lists: a row's k' best lie in the (at most k') slices whose best key
+    // is among the record keys' k' best (any other slice is beaten k' times
+    // over).  One slice per lane, then k' pops.
+    uint64_t lst[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) lst[i] = 0;
+    int nwin = 0;
+    uint64_t mykey = 0;
+    for (int e0 = 0; e0 < n; e0 += 64) {
+      const int e = e0 + lane;
+      const uint64_t key = e < n ? cand[e] : 0;
+      const bool head = e < n && (key & kTagMask) == 0 && cand_rank(cand, n, key) < kk;
+      uint64_t b = __ballot(head);
+      while (b) {
+        const int src = __builtin_ctzll(b);
+        b &= b - 1;
+        const uint64_t kx = readlane_u64(key, src);
+        if (lane == nwin) mykey = kx;
+        ++nwin;
+      }
+    }
+    const int myslice = lane < nwin ? child_key_token(mykey) / kTile % G : 0;
+    const uint64_t* src =
+        p.part_key + (((size_t)d * p.rows_max + row) * kSlicesMax + myslice) * p.kmax;
+    bool got = lane >= nwin, alive = true;
+    const long long t1 = wall_clock64();
+    for (int it = 0;; ++it) {
+      if (!got) {
+        bool ok = true;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          if (i < p.kmax) {
+            lst[i] = load_agent(src + i);
+            ok = ok && key_tagged(p, lst[i]);
+          }
+        }
+        got = ok;
+      }
+      if (__all(got)) break;
+      if (!wait_more(p, it, t1)) {
+        alive = false;
+        break;
+      }
+    }
+    if (!alive) continue;  // nothing is published: every other wait runs out too
+    for (int it = 0; it < kk; ++it) {
+      const uint64_t best = wave_max_u64(lst[0]);
+      if (lst[0] == best) {
+#pragma unroll
+        for (int i = 0; i + 1 < 16; ++i) lst[i] = lst[i + 1];
+        lst[15] = 0;
+      }
+      if (lane == 0) publish(it, best);
+    }
+  }
+}
+
+// The keepers of a round agree before any emits: all trees are emitted, or
+// (a keeper's wait ran out) every request is padded.  The word counts the
+// keepers that have their last stage; the first to give up marks it, after
+// which the count stays.  Called by one thread; ok: this keeper has all its
+// stages.
+constexpr uint64_t kAbandoned = 1ull << 32;
+__device__ __forceinline__ bool keepers_agree(const Plan& p, bool ok) {
+  if (p.R == 1) return ok;
+  if (ok) {
+    uint64_t old = load_agent(p.done_w);
+    for (;;) {
+      if (old & kAbandoned) return false;
+      if (__hip_atomic_compare_exchange_strong(p.done_w, &old, old + 1, __ATOMIC_RELAXED,
+                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+        break;
+    }
+    const long long t0 = wall_clock64();
+    for (int it = 0;; ++it) {
+      const uint64_t w = load_agent(p.done_w);
+      if ((uint32_t)w == (uint32_t)p.R) return true;
+      if (w & kAbandoned) return false;
+      if (!wait_more(p, it, t0)) break;
+    }
+  }
+  const uint64_t old =
+      __hip_atomic_fetch_or(p.done_w, kAbandoned, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return (uint32_t)old == (uint32_t)p.R;
+}
+
+// A keeper workgroup: one request's pool, trace and running top-N (in LDS),
+// stage by stage from the published children words, then its tree.
+struct KeepShared {
+  SelShared sel;
+  EmitShared emit;
+  int front_node[kNarrowRows], front_tok[kNarrowRows];
+  float front_score[kNarrowRows];
+  int go;
+  __attribute__((aligned(16))) uint64_t top_key[PCTREE_EMIT_MAX_N];
+  int top_node[PCTREE_EMIT_MAX_N];
+};
+
+__device__ __forceinline__ void keep_block(const Plan& p, KeepShared& ks, int req) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const State st{ks.front_node, ks.front_tok, ks.front_score, ks.top_key, ks.top_node, req};
+  init_request(p, req, tid, blockDim.x);
+  if (tid < p.kk) {
     const int r0 = p.root[req];
     const int root = r0 < 0 || r0 >= p.V ? 0 : r0;
-    st.top_key[(size_t)req * p.N] = node_key(0.0f, 0, root, 0);
-    st.top_node[(size_t)req * p.N] = 0;
-  }
-  if (threadIdx.x == 0) ssh.abort = 0;
-  __syncthreads();
-  for (int d = 0; d < p.B; ++d) {
-    // head rows of the stage (one per request in the control modes) and
-    // frontier parents (Sec. 5.3: the control modes' one row serves them all)
-    const int Ph = head_rows(p.mode, d, p.kk), Pf = d == 0 ? 1 : p.kk;
-    TIMELINE_STAMP(0, d, 0);
-    if (!sel_merge<KMAX>(p, d, p.R * Ph, ssh)) {
-      abort_outputs(p);
-      return;
+    ks.front_node[tid] = 0;
+    ks.front_tok[tid] = root;
+    ks.front_score[tid] = 0.0f;
+    if (tid == 0) {
+      ks.top_key[0] = node_key(0.0f, 0, root, 0);
+      ks.top_node[0] = 0;
+      ks.go = 1;
     }
-    TIMELINE_STAMP(0, d, 1);
-    if constexpr (kInline)
-      stage_select_body(p, st, d, Pf, 0, p.R, ssh, true, p.mode != 0);
-    else
-      stage_select(p, st, d, Pf, 0, p.R, ssh, true, p.mode != 0);
-    TIMELINE_STAMP(0, d, 2);
+  }
+  __syncthreads();
+  bool ok = true;
+  for (int d = 0; ok && d < p.B; ++d) {
+    // the words of the request's head rows (one row in the control modes,
+    // which serves every parent, Sec. 5.3)
+    const int n = head_rows(p.mode, d, p.kk) * p.kk;
+    if (req == 0) TIMELINE_STAMP(0, d, 0);
+    if (wave * 64 < n) {
+      uint64_t w;
+      if (!wait_word(p, cand_words(p, d) + req * n + min(tid, n - 1), w) && lane == 0) ks.go = 0;
+      if (tid < n) ks.sel.cword[tid] = w;
+    }
+    lds_barrier();
+    if (req == 0) TIMELINE_STAMP(0, d, 1);
+    ok = ks.go != 0;
+    if (ok) stage_select_body<true>(p, st, d, d == 0 ? 1 : p.kk, req, ks.sel, p.mode != 0);
+    if (req == 0) TIMELINE_STAMP(0, d, 2);
   }
   __syncthreads();  // the pool entries stored by the stages are visible to every wave
-  TIMELINE_STAMP(0, kTimelineStages - 1, 0);
-  for (int req = 0; req < p.R; ++req) {
-    if constexpr (kInline)
-      emit_request_body(p, st, req);
-    else
-      emit_request(p, st, req);
+  if (tid == 0) ks.go = keepers_agree(p, ok) ? 1 : 0;
+  __syncthreads();
+  if (!ks.go) {
+    abort_outputs(p, req);
+    return;
   }
-  TIMELINE_STAMP(0, kTimelineStages - 1, 1);
+  if (req == 0) TIMELINE_STAMP(0, kTimelineStages - 1, 0);
+  emit_request(p, st, req, ks.emit);
+  if (req == 0) TIMELINE_STAMP(0, kTimelineStages - 1, 1);
+}
+
+// All cross-workgroup words are written and read with agent-coherent
+// (L2-bypassing) accesses, and each is valid on its own (it carries the call's
+// tag), so no fence is needed anywhere.  The words are cleared before every
+// call.
+extern __shared__ __attribute__((aligned(16))) uint64_t g_dyn[];
+
+template <int DT, int NCMAX, bool R8>
+__global__ __launch_bounds__(kRoundWaves * 64) void round_kernel(Plan p) {
+  __shared__ FrontShared fs;
+  __shared__ RowShared rsh;
+  if (threadIdx.x == 0) {
+    fs.nsurv = 0;
+    fs.go = 1;
+  }
+  silu_tab_init(fs.tab);
+  lds_barrier();
+  const int b = blockIdx.x;
+  if (b < p.G)
+    stream_block<DT, NCMAX, R8>(p, fs, rsh, (char*)g_dyn);
+  else if (b < p.G + p.nmerge)
+    merge_block(p, fs, *(MergeShared*)g_dyn, b - p.G);
+  else
+    keep_block(p, *(KeepShared*)g_dyn, b - p.G - p.nmerge);
 }
 
 // ---------------------------------------------------------------------------
@@ -2468,7 +2889,7 @@ __device__ void select_tail(const Plan& p, int d, int P, int req, SelShared& ssh
   if (p.mode != 0 && threadIdx.x == 0) chain_tok[0] = child_key_token(ssh.rowkeys[0][0]);
   const int* toks = p.mode == 0 ? ssh.next_tok : chain_tok;
   u32x4 ev0 = {0u, 0u, 0u, 0u};
-  stage_select_body(p, st, d, Pf, req, 1, ssh, false, p.mode != 0, [&] {
+  stage_select_body<false>(p, st, d, Pf, req, ssh, p.mode != 0, [&] {
     lds_barrier();
     if (more) ev0 = next_e_first(p, Pn, toks);
   });
@@ -2651,28 +3072,6 @@ __device__ __forceinline__ void thr_exact(const Plan& p, int d, int P, int slice
     }
     __syncthreads();
   }
-}
-
-// 16 bytes per lane from global memory straight into LDS (lane l's bytes at
-// lds_dst + 16 l), counted in vmcnt like any vector-memory load.  Issued as
-// inline assembly: the compiler does not see the LDS write, so it does not
-// make later LDS reads wait for every load in flight (it cannot tell ring
-// slots apart); the kernel orders them itself with wait_vmcnt and a
-// barrier.  M0 holds the LDS base; nothing else in the kernels that use it
-// keeps a value in M0 across it.
-__device__ __forceinline__ void load_lds16(const void* src, const void* lds_dst) {
-  const uint32_t base = __builtin_amdgcn_readfirstlane(
-      (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)lds_dst);
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(base)
-               : "memory", "m0");
-}
-
-// s_waitcnt with only the vector-memory count limited (gfx9 encoding:
-// vmcnt bits 3:0 and 15:14, expcnt and lgkmcnt left at their maxima).
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-  static_assert(N >= 0 && N < 64, "vmcnt is 6 bits");
-  __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | 0x0F70);
 }
 
 // One V-slice for up to 128 frontier rows of a wide stage.  Wave w multiplies
@@ -3145,12 +3544,13 @@ __global__ __launch_bounds__(kSelectThreads) void mergesel_kernel(Plan p, int d,
   if (req == 0) TIMELINE_STAMP(4, d, 2);
 }
 
-// Zero the words the persistent round polls (slice partials of every stage,
-// row and slice, and the frontier words) and mark every request as not built.
+// Zero the words the persistent round polls (slice records and lists of every
+// stage, row and slice, and the children words) and mark every request as not
+// built.
 __global__ __launch_bounds__(256) void clear_kernel(Plan p) {
   const int per = p.kmax + kRecWords;  // list words, then record words
-  const int nrec = p.stages * p.rows_max * p.G;
-  const int n = nrec * per;
+  const int n = p.stages * p.rows_max * p.G * per;
+  const int nc = p.rows_max * p.kk;    // children words of a stage
   const int stride = gridDim.x * blockDim.x;
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
     const int rec = i / per, w = i - rec * per;
@@ -3160,13 +3560,15 @@ __global__ __launch_bounds__(256) void clear_kernel(Plan p) {
     else
       p.part_hd[((size_t)sr * kRecWords + (w - p.kmax)) * kSlicesMax + slice] = 0;
   }
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < p.stages * p.rows_max; i += stride)
-    p.front_w[i] = 0;
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < p.stages * nc; i += stride)
+    cand_words(p, i / nc)[i % nc] = 0;
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < p.R; i += stride) p.o_count[i] = -1;
+  if (blockIdx.x == 0 && threadIdx.x == 0) *p.done_w = 0;
 }
 
 __global__ __launch_bounds__(kEmitThreads) void emit_kernel(Plan p) {
-  emit_request(p, global_state(p), blockIdx.x);
+  __shared__ EmitShared es;
+  emit_request(p, global_state(p), blockIdx.x, es);
 }
 
 __global__ __launch_bounds__(kMaskThreads) void mask_kernel(const int* parent, const int* count,
@@ -3196,24 +3598,6 @@ typedef void (*RoundFn)(Plan);
     default: return KERNEL<DT, NCMAX, 16>;          \
   }
 
-// round kernels: KMAX up to 16 without fold, up to 8 with it
-#define PCTREE_ROUND_KMAX_SWITCH(KERNEL, DT, NCMAX, kmax, FOLD)        \
-  if (FOLD) {                                                         \
-    switch (kmax) {                                                   \
-      case 1: return KERNEL<DT, NCMAX, 1, true>;                      \
-      case 2: return KERNEL<DT, NCMAX, 2, true>;                      \
-      case 4: return KERNEL<DT, NCMAX, 4, true>;                      \
-      default: return KERNEL<DT, NCMAX, 8, true>;                     \
-    }                                                                 \
-  }                                                                   \
-  switch (kmax) {                                                     \
-    case 1: return KERNEL<DT, NCMAX, 1, false>;                       \
-    case 2: return KERNEL<DT, NCMAX, 2, false>;                       \
-    case 4: return KERNEL<DT, NCMAX, 4, false>;                       \
-    case 8: return KERNEL<DT, NCMAX, 8, false>;                       \
-    default: return KERNEL<DT, NCMAX, 16, false>;                     \
-  }
-
 #define PCTREE_DISPATCH(KERNEL, p)                                    \
   if ((p).dtype) {                                                    \
     if ((p).nchunk <= 4) { PCTREE_KMAX_SWITCH(KERNEL, 1, 4, (p).kmax) } \
@@ -3232,19 +3616,20 @@ int nchunk_max(const Plan& p) {
   if (p.dtype) return p.nchunk <= 4 ? 4 : (p.nchunk <= 8 ? 8 : (p.nchunk <= 12 ? 12 : 16));
   return p.nchunk <= 2 ? 2 : 8;
 }
-// The folded form serves rounds whose stages have at most 8 frontier rows.
-bool round_fold(const Plan& p) { return p.R * p.kk <= 8; }
+// Rounds of at most 8 frontier rows take the kernels with one row per wave.
+bool round_r8(const Plan& p) { return p.R * p.kk <= 8; }
 
 RoundFn round_fn(const Plan& p) {
-  const bool fold = round_fold(p);
-  if (p.dtype) {
-    if (p.nchunk <= 4) { PCTREE_ROUND_KMAX_SWITCH(round_kernel, 1, 4, p.kmax, fold) }
-    if (p.nchunk <= 8) { PCTREE_ROUND_KMAX_SWITCH(round_kernel, 1, 8, p.kmax, fold) }
-    if (p.nchunk <= 12) { PCTREE_ROUND_KMAX_SWITCH(round_kernel, 1, 12, p.kmax, fold) }
-    PCTREE_ROUND_KMAX_SWITCH(round_kernel, 1, 16, p.kmax, fold)
+  const bool r8 = round_r8(p);
+  switch (nchunk_max(p)) {
+    case 2: return r8 ? round_kernel<0, 2, true> : round_kernel<0, 2, false>;
+    case 4: return r8 ? round_kernel<1, 4, true> : round_kernel<1, 4, false>;
+    case 8:
+      if (p.dtype) return r8 ? round_kernel<1, 8, true> : round_kernel<1, 8, false>;
+      return r8 ? round_kernel<0, 8, true> : round_kernel<0, 8, false>;
+    case 12: return r8 ? round_kernel<1, 12, true> : round_kernel<1, 12, false>;
+    default: return r8 ? round_kernel<1, 16, true> : round_kernel<1, 16, false>;
   }
-  if (p.nchunk <= 2) { PCTREE_ROUND_KMAX_SWITCH(round_kernel, 0, 2, p.kmax, fold) }
-  PCTREE_ROUND_KMAX_SWITCH(round_kernel, 0, 8, p.kmax, fold)
 }
 
 StageFn mergesel_fn(int kmax) {
@@ -3313,36 +3698,35 @@ hipError_t launch_round(const Plan& p0, hipStream_t st) {
   if (narrow) {
     di = device_info();
     rfn = round_fn(p);
-    // one streaming slice per remaining CU (at most kSlicesMax) plus the
-    // selector block: every workgroup is resident at once
-    int target = std::max(1, std::min(di.cus - 1, kRoundSlicesMax));
+    // one mergers' workgroup per row (two rows with more than 8), one keeper
+    // per request and a streaming slice on every remaining CU: every workgroup
+    // is resident at once
+    const bool r8 = round_r8(p);
+    const int hrows = p.R * head_rows(p.mode, p.B - 1, p.kk);  // head rows of a stage at most
+    p.merge_rows = r8 ? 1 : 2;
+    p.nmerge = (hrows + p.merge_rows - 1) / p.merge_rows;
+    const int others = p.nmerge + p.R;
+    int target = std::max(1, std::min(di.cus - others, kRoundSlicesMax));
     if (dbg.round_slices > 0) target = std::min(target, dbg.round_slices);
     p.tiles_per_slice = (p.ntiles + target - 1) / target;
     p.G = (p.ntiles + p.tiles_per_slice - 1) / p.tiles_per_slice;
-    // dynamic LDS: the frontier's head input, the keeper's top-N, then as
-    // many resident W tiles as fit
+    // dynamic LDS: the frontier's head input and logits, then as many resident
+    // W tiles as fit; the mergers' and keepers' state in its place there
     const int ncmax = nchunk_max(p);
-    const size_t ubytes =
-        ((size_t)p.rows_max * (p.r * (p.dtype ? 2 : 4) + 16) + 255) & ~(size_t)255;
-    const size_t top = ubytes + (((size_t)p.R * p.N * (sizeof(uint64_t) + sizeof(int)) + 255) &
-                                 ~(size_t)255);
+    const size_t top = round_tile_offset(ncmax, r8);
     const size_t tile_bytes = (size_t)ncmax * 64 * 16;
     hipFuncAttributes attr{};
     int lds_max = 0;
     int dev = 0;
-    if (di.cus >= 2 && hipGetDevice(&dev) == hipSuccess &&
+    if (di.cus > others && hipGetDevice(&dev) == hipSuccess &&
         hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) ==
             hipSuccess &&
         hipFuncGetAttributes(&attr, (const void*)rfn) == hipSuccess) {
-      const long room = (long)lds_max - (long)attr.sharedSizeBytes - (long)top - 1024;
-      const int want =
-          std::max(0, p.tiles_per_slice - resident_reg_tiles(ncmax, round_fold(p)) * kRoundWaves);
-      const int cap = resident_lds_tiles_per_wave(ncmax) * kRoundWaves;
-      p.lds_tiles = room > 0 ? (int)std::min<long>({room / (long)tile_bytes, (long)want, (long)cap})
-                             : 0;
-      p.lds_top_offset = (int)ubytes;
-      p.lds_tile_offset = (int)top;
-      smem = top + (size_t)p.lds_tiles * tile_bytes;
+      const long room = (long)lds_max - (long)attr.sharedSizeBytes - (long)top;
+      const int want = std::max(0, p.tiles_per_slice - resident_reg_tiles(ncmax) * kRoundWaves);
+      p.lds_tiles = room > 0 ? (int)std::min<long>(room / (long)tile_bytes, (long)want) : 0;
+      smem = std::max({top + (size_t)p.lds_tiles * tile_bytes, sizeof(MergeShared),
+                       sizeof(KeepShared)});
       if (hipFuncSetAttribute((const void*)rfn, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)smem) != hipSuccess ||
           hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit, (const void*)rfn, kRoundWaves * 64,
@@ -3357,19 +3741,19 @@ hipError_t launch_round(const Plan& p0, hipStream_t st) {
     p.spin_ticks = dbg.wait_ticks >= 0 ? dbg.wait_ticks : 2 * di.ticks_per_s;
     // no word of an earlier use of the workspace may carry the call's tag
     {
-      const int n = p.stages * p.rows_max * p.G * (p.kmax + kRecWords) + p.stages * p.rows_max;
+      const int n = p.stages * p.rows_max * p.G * (p.kmax + kRecWords);
       hipLaunchKernelGGL(clear_kernel, dim3(std::min((n + 255) / 256, 2048)), dim3(256), 0, st,
                          p);
     }
     void* args[] = {&p};
     const bool prof = profile_on();
     if (prof) profile_mark(st, "round_kernel");
-    // An ordinary launch: the G + 1 workgroups (at most one per CU, checked
+    // An ordinary launch: the workgroups (at most one per CU, checked
     // above) are all resident on an otherwise idle device.  A cooperative
     // launch would guarantee it even beside other work, but costs ~18 us of
     // dispatch per call here; with other kernels on the device a workgroup
     // may start late, which the bounded waits absorb (or the round aborts).
-    const hipError_t e = hipLaunchKernel((const void*)rfn, dim3(p.G + 1),
+    const hipError_t e = hipLaunchKernel((const void*)rfn, dim3(p.G + p.nmerge + p.R),
                                          dim3(kRoundWaves * 64), args, smem, st);
     if (prof) profile_mark(st, "round_kernel");
     if (e != hipSuccess) return e;

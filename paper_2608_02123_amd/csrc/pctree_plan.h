@@ -10,14 +10,14 @@ namespace pctree {
 
 constexpr int kTile = 16;           // tokens per MFMA output tile (M of 16x16xK)
 constexpr int kSlicesMax = 512;     // V-slices of one head launch
-constexpr int kRoundSlicesMax = 256;  // V-slices of the persistent round kernel
+constexpr int kRoundSlicesMax = 256;  // V-slices of the persistent round kernel (the rest of a
+                                      // stage's list buffer then holds its children words)
 constexpr int kHeadThreads = 256;   // 4 waves
 constexpr int kSelectThreads = 1024;
 constexpr int kEmitThreads = 256;
 constexpr int kMaskThreads = 256;
 constexpr int kRoundWaves = 8;       // waves per WG of the persistent round kernel
 constexpr int kNarrowRows = 16;      // frontier rows (R * k') one column block holds
-constexpr int kFlagStride = 64;      // ints between two workgroups' flag words (256 B)
 constexpr int kProbe = 32;           // probe tokens per (request, depth) of the wide stages
 
 // What a streaming workgroup publishes per (stage, row, slice) besides its
@@ -79,7 +79,7 @@ struct Plan {
   uint64_t* part_key;// [stages][rows_max][kSlicesMax][kmax] per-slice candidate lists
   uint64_t* part_hd; // [stages][rows_max][kRecWords][kSlicesMax] slice records
   int* req_bad;      // [R] root token outside [0, V)
-  uint64_t* front_w; // [stages][rows_max] frontier of each stage (persistent form)
+  uint64_t* done_w;  // keepers of the persistent form that have their last stage
   float* tau;        // [rows_max] wide stages: lower bound of each row's k'-th best logit
   int* probe_tok;    // [R][B][kProbe] wide stages: probe tokens of each request and depth
   void* probe_w;     // [R][B][kProbe][r] (dtype) their W rows (zero for a missing probe)
@@ -90,9 +90,9 @@ struct Plan {
   int mode;          // 0 parent-conditioned, 1 Shared-Markov, 2 parent-independent
   int unbounded;     // wide stages ignore tau (every logit is a candidate)
   long long spin_ticks;  // device wall-clock ticks a wait may last before aborting
-  int lds_tiles;         // W tiles a streaming block keeps in LDS for the whole round
-  int lds_top_offset;    // byte offset of the keeper's running top-N in the dynamic LDS
-  int lds_tile_offset;   // byte offset of the resident W tiles in the dynamic LDS
+  int lds_tiles;         // W tiles a streaming workgroup keeps in LDS for the whole round
+  int kk_inv;            // 65536 / kk + 1 (division by kk in the kernels)
+  int nmerge, merge_rows;  // merger workgroups of the persistent form, and rows of each
 };
 
 // Workspace layout for a plan; offsets are 256-byte aligned.  With base ==

@@ -3,9 +3,9 @@
 ``libpctree_timeline.so`` is the library with device wall-clock stamps at the
 steps of every stage (include/pctree_profile.h lists them).  This tool runs a
 few rounds of a synthetic workload through it, reads the stamps of the last
-round and prints where the round's time goes: per stage, the keeper's merge
-and selection and the first and last streaming workgroups' wait, head input,
-stream and publish (single-launch round), or the wide stages' head and
+round and prints where the round's time goes: per stage, the keeper's wait for
+the merged rows and its selection, and the first and last streaming workgroups'
+wait and head input, stream and publish (single-launch round), or the wide stages' head and
 merge-and-select launches (per-stage launches).
 
     python -m paper_2608_02123_amd.timeline [--workload qwen4b_b16]

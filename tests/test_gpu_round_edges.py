@@ -1,0 +1,110 @@
+"""The single-launch round at the edges of its work split, against the oracle.
+
+Slices of one tile per wave, of exactly one LDS batch of logits (40 tiles) and
+of one tile more; every branching factor at which a path changes (one child,
+the record's three keys, the candidate pruning from k' = 12); many requests
+with a keeper each; ranks that leave padded chunks.  Two more inputs take the
+rare paths: the best tokens of every row in one tile (a slice gives up its
+whole record, so the merger reads the full lists) and logits that are all
+equal (more candidates than the row phase ranks at once).  The vocabulary is
+sliced over few workgroups by the test-only launch override, so that small
+vocabularies reach the large slices.
+"""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2608_02123_amd import pctree as P
+from paper_2608_02123_amd.synth import Workload, make_inputs
+import compare as C
+
+pytestmark = pytest.mark.gpu
+
+# V, B, N, k, r, R, dtype, slices at most (0: one per compute unit)
+SHAPES = [
+    (3 * 8 * 16, 3, 24, 8, 32, 1, "bf16", 3),        # one tile per wave
+    (3 * 9 * 16 - 7, 3, 24, 8, 32, 1, "bf16", 3),    # one more, ragged
+    (3 * 40 * 16, 4, 40, 8, 64, 1, "bf16", 3),       # exactly one batch of logits
+    (3 * 41 * 16 - 3, 4, 40, 8, 64, 1, "bf16", 3),   # one tile in a second batch
+    (2 * 90 * 16 + 5, 3, 60, 16, 96, 1, "f32", 2),   # three batches, 16 rows
+    (4099, 4, 30, 3, 288, 1, "bf16", 0),             # k' = the record's keys
+    (4099, 4, 30, 4, 512, 1, "bf16", 0),             # one more: lists
+    (4099, 3, 64, 12, 352, 1, "bf16", 0),            # pruned layers, padded chunks
+    (4099, 5, 20, 1, 128, 16, "f32", 0),             # 16 requests, chains
+    (2050, 4, 20, 2, 16, 8, "f32", 0),
+    (2050, 4, 33, 3, 160, 5, "bf16", 0),             # a wave's rows of two requests
+    (9001, 3, 50, 8, 256, 2, "bf16", 0),             # 128 candidates
+    (70001, 3, 30, 8, 384, 1, "bf16", 61),           # tiles read again every stage
+]
+
+
+def _run(w, inp, slices=0, mode=P.MODE_PARENT):
+    dev = P.device_inputs(inp)
+    b = P.TreeBuilder(w.V, w.B, w.N, w.k, w.r, w.R, P.BF16 if w.dtype == "bf16" else P.F32,
+                      mask=True, trace=True, mode=mode)
+    P.debug_set(round_slices=slices)
+    try:
+        out = b.run(**dev, check=True)
+        torch.cuda.synchronize()
+    finally:
+        P.debug_set()
+    return out
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "V{}B{}N{}k{}r{}R{}{}s{}".format(*s))
+def test_edges(shape):
+    V, B, N, k, r, R, dt, slices = shape
+    print(f"[edges] {shape}", flush=True)
+    w = Workload("edge", V=V, B=B, N=N, k=k, r=r, R=R, dtype=dt, peak="uniform", seed=5)
+    inp = make_inputs(w)
+    out = _run(w, inp, slices)
+    reps = C.compare_batch(out, inp, k, N, label=f"edges {shape}")
+    assert all(rep["exact"] or rep["identical"] for rep in reps), reps
+
+
+@pytest.mark.parametrize("k", [4, 8, 16])
+@pytest.mark.parametrize("mode", ["parent", "shared", "independent"])
+def test_best_tokens_in_one_tile(k, mode):
+    """The 14 best tokens of every depth share a tile: more than a record holds."""
+    print(f"[edges] one tile k={k} {mode}", flush=True)
+    w = Workload("tile", V=5000, B=4, N=60, k=k, r=64, R=1, dtype="bf16", peak="none", seed=6)
+    inp = make_inputs(w)
+    inp["L"][:, :, 1601:1615] += np.float32(32.0) + 4 * np.arange(14, dtype=np.float32)
+    inp["L"] = torch.from_numpy(inp["L"]).bfloat16().float().numpy()
+    m = {"parent": P.MODE_PARENT, "shared": P.MODE_SHARED, "independent": P.MODE_INDEPENDENT}[mode]
+    out = _run(w, inp, mode=m)
+    reps = C.compare_batch(out, inp, k, w.N, mode=mode, label=f"one tile k={k} {mode}")
+    # (parent-independent scores tie exactly: a + b = b + a across parents)
+    assert all(rep["exact"] or rep["identical"] for rep in reps), reps
+
+
+@pytest.mark.parametrize("V,slices", [(3000, 0), (3000, 2), (2 * 41 * 16, 2)])
+def test_equal_logits(V, slices):
+    """Every logit equal: ties go to the lowest token, on every path."""
+    print(f"[edges] equal logits V={V} slices={slices}", flush=True)
+    w = Workload("flat", V=V, B=3, N=40, k=8, r=32, R=1, dtype="f32", peak="none", seed=7,
+                 sigma_L=0.0, sigma_W=0.0)
+    inp = make_inputs(w)
+    out = _run(w, inp, slices)
+    reps = C.compare_batch(out, inp, w.k, w.N, label="equal logits")
+    assert all(rep["identical"] for rep in reps), reps
+
+
+def test_abandoned_round_of_many_requests_pads_all():
+    """Every keeper gives up when one does: no request keeps a tree."""
+    print("[edges] abandoned round, 8 requests", flush=True)
+    w = Workload("abort", V=4099, B=4, N=12, k=2, r=32, R=8, dtype="bf16", peak="uniform", seed=8)
+    dev = P.device_inputs(make_inputs(w))
+    b = P.TreeBuilder(w.V, w.B, w.N, w.k, w.r, w.R, P.BF16, mask=True)
+    P.debug_set(wait_ticks=0)
+    try:
+        out = b.run(**dev)
+        torch.cuda.synchronize()
+    finally:
+        P.debug_set()
+    assert (out["count"] == -1).all()
+    assert (out["token"] == -1).all() and (out["mask"] == 0).all()
+    out = b.run(**dev, check=True)
+    assert (out["count"] == w.N).all()  # (a pool of 1 + k + 3 k^2 = 15 nodes)

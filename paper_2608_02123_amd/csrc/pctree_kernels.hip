@@ -35,6 +35,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <mutex>
 #include <type_traits>
 
 #define PCTREE_EMIT_MAX_N 256
@@ -3619,17 +3620,17 @@ int nchunk_max(const Plan& p) {
 // Rounds of at most 8 frontier rows take the kernels with one row per wave.
 bool round_r8(const Plan& p) { return p.R * p.kk <= 8; }
 
-RoundFn round_fn(const Plan& p) {
-  const bool r8 = round_r8(p);
-  switch (nchunk_max(p)) {
-    case 2: return r8 ? round_kernel<0, 2, true> : round_kernel<0, 2, false>;
-    case 4: return r8 ? round_kernel<1, 4, true> : round_kernel<1, 4, false>;
-    case 8:
-      if (p.dtype) return r8 ? round_kernel<1, 8, true> : round_kernel<1, 8, false>;
-      return r8 ? round_kernel<0, 8, true> : round_kernel<0, 8, false>;
-    case 12: return r8 ? round_kernel<1, 12, true> : round_kernel<1, 12, false>;
-    default: return r8 ? round_kernel<1, 16, true> : round_kernel<1, 16, false>;
-  }
+constexpr int kRoundFns = 12;
+const RoundFn kRoundFn[kRoundFns] = {
+    round_kernel<0, 2, true>,   round_kernel<0, 2, false>,  round_kernel<0, 8, true>,
+    round_kernel<0, 8, false>,  round_kernel<1, 4, true>,   round_kernel<1, 4, false>,
+    round_kernel<1, 8, true>,   round_kernel<1, 8, false>,  round_kernel<1, 12, true>,
+    round_kernel<1, 12, false>, round_kernel<1, 16, true>,  round_kernel<1, 16, false>};
+
+// Index of the round's kernel in kRoundFn.
+int round_index(const Plan& p) {
+  const int n = nchunk_max(p);
+  return (p.dtype ? 4 + 2 * (n / 4 - 1) : (n == 2 ? 0 : 2)) + (round_r8(p) ? 0 : 1);
 }
 
 StageFn mergesel_fn(int kmax) {
@@ -3658,25 +3659,45 @@ uint32_t next_tag() {
   return seq.fetch_add(1, std::memory_order_relaxed) % kTagMask + 1;
 }
 
-// Per-device facts for the persistent launch, queried once per device.
+// Per-device facts for the persistent launch, queried once per device (and
+// kernel): asking the runtime on every call took longer than enqueuing it.
 struct DeviceInfo {
   int cus = 0;
   long long ticks_per_s = 0;
+  size_t lds_free[kRoundFns] = {};  // dynamic LDS each round kernel may use (0: does not run)
 };
 
-DeviceInfo device_info() {
+const DeviceInfo& device_info() {
+  static const DeviceInfo none;
   static DeviceInfo cache[64];
+  static std::once_flag once[64];
   int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return DeviceInfo{};
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return none;
   DeviceInfo& di = cache[dev];
-  if (di.cus == 0) {
-    int cus = 0, khz = 0;
+  std::call_once(once[dev], [&di, dev] {
+    int cus = 0, khz = 0, lds = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
       cus = 0;
     if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev) != hipSuccess) khz = 0;
+    if (hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
+      lds = 0;
     di.ticks_per_s = (long long)(khz > 0 ? khz : 100000) * 1000;
     di.cus = cus;
-  }
+    for (int i = 0; i < kRoundFns; ++i) {
+      const void* fn = (const void*)kRoundFn[i];
+      hipFuncAttributes attr{};
+      int fit = 0;
+      if (hipFuncGetAttributes(&attr, fn) != hipSuccess || lds <= (int)attr.sharedSizeBytes)
+        continue;
+      const int room = lds - (int)attr.sharedSizeBytes;
+      if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, room) ==
+              hipSuccess &&
+          hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit, fn, kRoundWaves * 64, room) ==
+              hipSuccess &&
+          fit > 0)
+        di.lds_free[i] = room;
+    }
+  });
   return di;
 }
 
@@ -3691,13 +3712,11 @@ hipError_t launch_round(const Plan& p0, hipStream_t st) {
   const DebugConfig dbg = debug_config();
   const bool narrow = p0.R * p0.kk <= kNarrowRows && !dbg.force_multilaunch;
   Plan p = p0;
-  DeviceInfo di;
+  const DeviceInfo& di = device_info();
   RoundFn rfn = nullptr;
   int fit = 0;
   size_t smem = 0;
   if (narrow) {
-    di = device_info();
-    rfn = round_fn(p);
     // one mergers' workgroup per row (two rows with more than 8), one keeper
     // per request and a streaming slice on every remaining CU: every workgroup
     // is resident at once
@@ -3715,23 +3734,16 @@ hipError_t launch_round(const Plan& p0, hipStream_t st) {
     const int ncmax = nchunk_max(p);
     const size_t top = round_tile_offset(ncmax, r8);
     const size_t tile_bytes = (size_t)ncmax * 64 * 16;
-    hipFuncAttributes attr{};
-    int lds_max = 0;
-    int dev = 0;
-    if (di.cus > others && hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) ==
-            hipSuccess &&
-        hipFuncGetAttributes(&attr, (const void*)rfn) == hipSuccess) {
-      const long room = (long)lds_max - (long)attr.sharedSizeBytes - (long)top;
+    const int index = round_index(p);
+    rfn = kRoundFn[index];
+    const size_t lds_free = di.cus > others ? di.lds_free[index] : 0;
+    if (lds_free > 0) {
+      const long room = (long)lds_free - (long)top;
       const int want = std::max(0, p.tiles_per_slice - resident_reg_tiles(ncmax) * kRoundWaves);
       p.lds_tiles = room > 0 ? (int)std::min<long>(room / (long)tile_bytes, (long)want) : 0;
       smem = std::max({top + (size_t)p.lds_tiles * tile_bytes, sizeof(MergeShared),
                        sizeof(KeepShared)});
-      if (hipFuncSetAttribute((const void*)rfn, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)smem) != hipSuccess ||
-          hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit, (const void*)rfn, kRoundWaves * 64,
-                                                       smem) != hipSuccess)
-        fit = 0;
+      fit = smem <= lds_free ? 1 : 0;
     }
   }
   p.tag = next_tag();

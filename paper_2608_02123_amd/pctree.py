@@ -7,6 +7,7 @@ library has not been built this module raises; there is no fallback path.
 from __future__ import annotations
 
 import ctypes
+import math
 import os
 
 import torch
@@ -167,13 +168,17 @@ def _check(status: int, what: str) -> None:
         raise PCTreeError(status, what)
 
 
+# (addresses go to the C entry points as plain integers, which their argument
+# types convert: wrapping each one, and a stream object per call, took as long
+# as a small kernel)
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream=None):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _dtype_code(t: torch.Tensor) -> int:
@@ -203,25 +208,26 @@ def check_inputs(shape: Shape, L, E, Wt, h, root, prefix_len, *, device=True) ->
     tensors by the shape alone, so a smaller tensor would be read past its end.
     """
     V, B, r, R = shape.vocab, shape.block, shape.rank, shape.requests
-    want = {
-        "L": (L, (R, B, V), _TORCH_DTYPE.get(shape.dtype)),
-        "E": (E, (V, r), _TORCH_DTYPE.get(shape.dtype)),
-        "Wt": (Wt, (V, r), _TORCH_DTYPE.get(shape.dtype)),
-        "h": (h, (R, B, r), torch.float32),
-        "root": (root, (R,), torch.int32),
-        "prefix_len": (prefix_len, (R,), torch.int32),
-    }
-    for name, (t, shp, dt) in want.items():
-        if not isinstance(t, torch.Tensor):
-            raise TypeError(f"{name} must be a torch tensor")
-        if dt is None or t.dtype != dt:
-            raise TypeError(f"{name} must be {dt}, got {t.dtype}")
-        if tuple(t.shape) != shp:
-            raise ValueError(f"{name} must have shape {shp}, got {tuple(t.shape)}")
-        if not t.is_contiguous():
-            raise ValueError(f"{name} must be contiguous")
-        if device and not t.is_cuda:
-            raise ValueError(f"{name} must be a device tensor")
+    dt = _TORCH_DTYPE.get(shape.dtype)
+    _check_input("L", L, (R, B, V), dt, device)
+    _check_input("E", E, (V, r), dt, device)
+    _check_input("Wt", Wt, (V, r), dt, device)
+    _check_input("h", h, (R, B, r), torch.float32, device)
+    _check_input("root", root, (R,), torch.int32, device)
+    _check_input("prefix_len", prefix_len, (R,), torch.int32, device)
+
+
+def _check_input(name, t, shp, dt, device):
+    if not isinstance(t, torch.Tensor):
+        raise TypeError(f"{name} must be a torch tensor")
+    if dt is None or t.dtype != dt:
+        raise TypeError(f"{name} must be {dt}, got {t.dtype}")
+    if t.shape != shp:
+        raise ValueError(f"{name} must have shape {shp}, got {tuple(t.shape)}")
+    if not t.is_contiguous():
+        raise ValueError(f"{name} must be contiguous")
+    if device and not t.is_cuda:
+        raise ValueError(f"{name} must be a device tensor")
 
 
 def _inputs(shape, L, E, Wt, h, root, prefix_len):
@@ -293,7 +299,7 @@ class TreeBuilder:
     def launch(self, stream=None, check=False):
         if self.workspace is None:
             raise RuntimeError("this builder has no workspace: use run_noalloc()")
-        st = lib().pctree_build_tree(*self._args, ctypes.c_void_p(self.workspace.data_ptr()),
+        st = lib().pctree_build_tree(*self._args, self.workspace.data_ptr(),
                                      self.workspace.numel(), _stream(stream))
         _check(st, "pctree_build_tree")
         if check:
@@ -395,7 +401,7 @@ def chain_decode(L, E, Wt, h, root, prefix_len=None, stream=None, mode=MODE_PARE
     lps = torch.empty(R, B + 1, dtype=torch.float32, device=L.device)
     inp = _inputs(shape, L, E, Wt, h, root, prefix_len)
     st = lib().pctree_chain_decode(ctypes.byref(shape), ctypes.byref(inp), _ptr(toks), _ptr(lps),
-                                   ctypes.c_void_p(ws.data_ptr()), ws.numel(), _stream(stream))
+                                   ws.data_ptr(), ws.numel(), _stream(stream))
     _check(st, "pctree_chain_decode")
     return toks, lps
 
@@ -410,8 +416,9 @@ def build_retrieve(parent, count, max_depth, stream=None):
     _int32_dev("parent", parent)
     _int32_dev("count", count)
     R, N = parent.shape
-    rows = torch.empty(R, N, max_depth + 1, dtype=torch.int32, device=parent.device)
-    nrows = torch.empty(R, dtype=torch.int32, device=parent.device)
+    dev = parent.device
+    rows = torch.empty((R, N, max_depth + 1), dtype=torch.int32, device=dev)
+    nrows = torch.empty((R,), dtype=torch.int32, device=dev)
     st = lib().pctree_build_retrieve(_ptr(parent), _ptr(count), R, N, max_depth, _ptr(rows),
                                      _ptr(nrows), _stream(stream))
     _check(st, "pctree_build_retrieve")
@@ -425,7 +432,7 @@ def accept_greedy(token, rows, nrows, target_next, stream=None):
                     ("target_next", target_next)):
         _int32_dev(name, t)
     R, N, W = rows.shape
-    if tuple(token.shape) != (R, N) or tuple(target_next.shape) != (R, N):
+    if token.shape != (R, N) or target_next.shape != (R, N):
         raise ValueError("token and target_next must be [R][N] like the rows")
     i32 = dict(dtype=torch.int32, device=rows.device)
     out = {"accept_len": torch.empty(R, **i32), "accept_row": torch.empty(R, **i32),
@@ -450,7 +457,7 @@ def compact_kv(cache, prefix_len, accept_node, accept_len, budget, stream=None):
         _int32_dev(name, t)
     R, G, T = cache.shape[:3]
     es = cache.element_size()
-    slot = cache[0, 0, 0].numel() * es
+    slot = math.prod(cache.shape[3:]) * es
     st = lib().pctree_compact_kv(_ptr(cache), cache.stride(0) * es, cache.stride(1) * es, G, T,
                                  slot, _ptr(prefix_len), _ptr(accept_node), _ptr(accept_len), R,
                                  budget, accept_node.shape[1] - 1, _stream(stream))
@@ -481,17 +488,17 @@ class TreeAttention:
         for name, t, shp in (("q", q, (R, N, Hq, D)), ("k", k, (R, Hkv, C, D)),
                              ("v", v, (R, Hkv, C, D))):
             if t.dtype != torch.bfloat16 or not t.is_cuda or not t.is_contiguous() \
-                    or tuple(t.shape) != shp:
+                    or t.shape != shp:
                 raise ValueError(f"{name} must be a contiguous bf16 device tensor {shp}")
         if mask.dtype != torch.int32 and mask.dtype != torch.uint32:
             raise TypeError("mask must be the [R][N][(N+31)/32] words of build_mask")
-        if tuple(mask.shape) != (R, N, (N + 31) // 32) or not mask.is_contiguous() \
+        if mask.shape != (R, N, (N + 31) // 32) or not mask.is_contiguous() \
                 or not mask.is_cuda:
             raise ValueError("mask must be [R][N][(N+31)/32] and contiguous")
         _int32_dev("count", count)
         _int32_dev("prefix_len", prefix_len)
         if out is None:
-            out = torch.empty(R, N, Hq, D, dtype=torch.bfloat16, device=q.device)
+            out = torch.empty((R, N, Hq, D), dtype=torch.bfloat16, device=q.device)
         st = lib().pctree_tree_attention(ctypes.byref(s), _ptr(q), _ptr(k), _ptr(v), _ptr(mask),
                                          _ptr(count), _ptr(prefix_len), _ptr(out),
                                          _ptr(self.workspace), self.ws_bytes, _stream(stream))

@@ -171,12 +171,6 @@ __device__ __forceinline__ float silu_fast(float e, float h, bool& ok) {
        (b & 0x7f800000u) != 0u;
   return y;
 }
-__device__ __forceinline__ uint16_t silu_bf16(float e, float h) {
-  bool ok;
-  const float y = silu_fast(e, h, ok);
-  return bf16_rne(ok ? y : silu_f32(e, h));
-}
-
 template <int DT>
 __device__ __forceinline__ float load_elem(const void* base, size_t i) {
   if (DT) return __uint_as_float((uint32_t)((const uint16_t*)base)[i] << 16);
@@ -2718,16 +2712,37 @@ __device__ void next_inputs(const Plan& p, int d, int P, int req, const int* tok
       if (p.dtype) {
         const f32x4 h0 = *(const f32x4*)(hrow + 8 * k), h1 = *(const f32x4*)(hrow + 8 * k + 4);
         const float hv[8] = {h0[0], h0[1], h0[2], h0[3], h1[0], h1[1], h1[2], h1[3]};
+        // (the float64 path once, in a loop over the few elements that need it:
+        // a copy per element made most of this kernel's code, which every
+        // launch fetches anew)
+        uint32_t bad = 0;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
-          const uint16_t lo = silu_bf16(__uint_as_float(ev[w] << 16), hv[2 * w]);
-          const uint16_t hi = silu_bf16(__uint_as_float(ev[w] & 0xffff0000u), hv[2 * w + 1]);
-          out[w] = (uint32_t)lo | ((uint32_t)hi << 16);
+        for (int i = 0; i < 8; ++i) {
+          bool ok;
+          const float e = __uint_as_float((i & 1) ? ev[i / 2] & 0xffff0000u : ev[i / 2] << 16);
+          const uint32_t u = bf16_rne(silu_fast(e, hv[i], ok));
+          out[i / 2] |= u << (16 * (i & 1));
+          bad |= ok ? 0u : 1u << i;
+        }
+        while (bad) {
+          const int i = __builtin_ctz(bad);
+          bad &= bad - 1;
+          const uint32_t ew = i < 4 ? (i < 2 ? ev[0] : ev[1]) : (i < 6 ? ev[2] : ev[3]);
+          const uint32_t u = bf16_rne(
+              silu_f32(__uint_as_float((i & 1) ? ew & 0xffff0000u : ew << 16), hrow[8 * k + i]));
+          const uint32_t clear = (i & 1) ? 0x0000ffffu : 0xffff0000u, put = u << (16 * (i & 1));
+#pragma unroll
+          for (int w = 0; w < 4; ++w)
+            if (w == i / 2) out[w] = (out[w] & clear) | put;
         }
       } else {
-        const f32x4 h0 = *(const f32x4*)(hrow + 4 * k);
+#pragma unroll 1
+        for (int i = 0; i < 4; ++i) {
+          const uint32_t ew = i < 2 ? (i < 1 ? ev[0] : ev[1]) : (i < 3 ? ev[2] : ev[3]);
+          const uint32_t u = __float_as_uint(silu_f32(__uint_as_float(ew), hrow[4 * k + i]));
 #pragma unroll
-        for (int w = 0; w < 4; ++w) out[w] = __float_as_uint(silu_f32(__uint_as_float(ev[w]), h0[w]));
+          for (int w = 0; w < 4; ++w) out[w] = w == i ? u : out[w];
+        }
       }
     }
     *(u32x4*)&nx.u[s * words + 4 * k] = out;
@@ -2967,6 +2982,7 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(Plan p, int d, i
 }
 
 constexpr int kWideWaves = 8;       // waves of a wide head workgroup
+constexpr int kWideSlices = 256;    // V-slices of a stage at most (plan_shape)
 constexpr int kThrRows = kWideWaves * kTile;  // rows of one column group: 8 blocks of 16
 constexpr int kThrSlots = 4;        // super-tiles (two W tiles) in the LDS ring
 constexpr int kLUnits = 64;         // 16-byte units of L_d per ring slot (one load instruction)
@@ -3099,6 +3115,7 @@ __global__ __launch_bounds__(kWideWaves * 64) void head_thr_kernel(Plan p, int d
   constexpr int LW = DT ? 2 : 4;     // 32-bit words of L_d per row and tile per lane
   constexpr int GROUP = CPW + 2;     // vector-memory instructions per super-tile per wave
   typedef uint32_t lvec __attribute__((ext_vector_type(LW)));
+  typedef lvec lvec_any __attribute__((aligned(ESZ)));  // (at any element)
   __shared__ u32x4 ring0[SH::kSlot0], ring1[SH::kSlot], ring2[SH::kSlot], ring3[SH::kSlot];
   __shared__ u32x4 lslot[kThrSlots][kLUnits];  // L_d of the group's requests per super-tile
   __shared__ uint64_t cand[kThrRows * KMAX];  // each row's candidates
@@ -3161,8 +3178,6 @@ __global__ __launch_bounds__(kWideWaves * 64) void head_thr_kernel(Plan p, int d
   const int ru = p.r * ESZ / 16;  // 16-byte units of a W row (a multiple of 4, at most 64)
   const char* lrow0 = (const char*)p.L + ((size_t)q0 * p.B + d) * p.V * ESZ;
   const char* lrow1 = (const char*)p.L + ((size_t)q1 * p.B + d) * p.V * ESZ;
-  // whether 16-bit L_d rows allow one aligned vector load of four tokens
-  const bool lvec_ok = ((size_t)p.V * ESZ) % (LW * 4) == 0;
 
   // One super-tile's loads: its 32 token rows of W straight into its ring
   // slot, one row per instruction (lane l loads the row's l-th 16 bytes, so
@@ -3194,20 +3209,21 @@ __global__ __launch_bounds__(kWideWaves * 64) void head_thr_kernel(Plan p, int d
       }
     } else {
       const int t = min(t0 + 2 * s + half, t1 - 1);
-      const int tb = min(t * kTile + lg * 4, p.V - 4 > 0 ? p.V - 4 : 0);
-      if (lvec_ok && p.V >= 4) {
-        l[0] = *(const lvec*)(lrow0 + (size_t)tb * ESZ);
-        l[1] = *(const lvec*)(lrow1 + (size_t)tb * ESZ);
-      } else {  // (unaligned rows: word by word)
+      const int tb = min(t * kTile + lg * 4, max(p.V - 4, 0));
+      if (p.V >= 4) {
+        // (one load of four tokens per row, at any alignment: token by token,
+        // the loads outran what the ring's waits count, and each step waited
+        // for the next ones' W)
+        l[0] = *(const lvec_any*)(lrow0 + (size_t)tb * ESZ);
+        l[1] = *(const lvec_any*)(lrow1 + (size_t)tb * ESZ);
+      } else {  // (fewer tokens than one load takes)
         lvec a, b;
 #pragma unroll
         for (int i = 0; i < LW; ++i) { a[i] = 0u; b[i] = 0u; }
-        const int tb2 = t * kTile + lg * 4;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const int v = min(tb2 + i, p.V - 1);
-          const uint32_t ra = load_raw<DT>(p.L, ((size_t)q0 * p.B + d) * p.V + v);
-          const uint32_t rb = load_raw<DT>(p.L, ((size_t)q1 * p.B + d) * p.V + v);
+          const int v = min(i, p.V - 1);
+          const uint32_t ra = load_raw<DT>(lrow0, v), rb = load_raw<DT>(lrow1, v);
           if (DT) {
             a[i / 2] |= ra << (16 * (i & 1));
             b[i / 2] |= rb << (16 * (i & 1));
@@ -3225,7 +3241,7 @@ __global__ __launch_bounds__(kWideWaves * 64) void head_thr_kernel(Plan p, int d
   // tile, realigned when a register vector load had to start earlier)
   auto lval = [&](auto ll, const lvec& l, int tb, int i) __attribute__((always_inline)) -> float {
     constexpr bool LL = decltype(ll)::value;
-    const int shift = (!LL && lvec_ok && p.V >= 4) ? tb - min(tb, p.V - 4 > 0 ? p.V - 4 : 0) : 0;
+    const int shift = !LL && p.V >= 4 ? tb - min(tb, p.V - 4) : 0;
     const int e = min(i + shift, 3);
     return DT ? __uint_as_float((e & 1) ? (l[e / 2] & 0xffff0000u) : (l[e / 2] << 16))
               : __uint_as_float(l[e]);
@@ -3448,10 +3464,10 @@ __global__ __launch_bounds__(kSelectThreads) void mergesel_kernel(Plan p, int d,
   const int req = blockIdx.x;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   if (req == 0) TIMELINE_STAMP(4, d, 0);
-  // the lane's slices of its wave's row (at most kSlicesMax / 64):
+  // the lane's slices of its wave's row:
   // statistics and counts first, all loads in flight together, then the
   // state and next-stage loads behind them, then the few candidates
-  constexpr int SPL = kSlicesMax / 64;
+  constexpr int SPL = kWideSlices / 64;
   const int gr = req * P + min(wave, P - 1);
   float2 v[SPL];
   int c[SPL];

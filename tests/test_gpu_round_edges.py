@@ -108,3 +108,20 @@ def test_abandoned_round_of_many_requests_pads_all():
     assert (out["token"] == -1).all() and (out["mask"] == 0).all()
     out = b.run(**dev, check=True)
     assert (out["count"] == w.N).all()  # (a pool of 1 + k + 3 k^2 = 15 nodes)
+
+
+# V, B, N, k, r, R, dtype: more than 16 frontier rows, base logits at any
+# alignment (and vocabularies below one load of four tokens)
+WIDE = [(3, 3, 12, 3, 32, 6, "bf16"), (5, 3, 20, 5, 16, 4, "f32"), (1001, 3, 30, 6, 96, 3, "bf16"),
+        (1002, 3, 30, 2, 64, 17, "bf16"), (1003, 3, 30, 9, 48, 2, "f32"), (4100, 3, 40, 16, 32, 2, "bf16")]
+
+
+@pytest.mark.parametrize("shape", WIDE, ids=lambda s: "V{}B{}N{}k{}r{}R{}{}".format(*s))
+def test_wide_rows_at_any_alignment(shape):
+    V, B, N, k, r, R, dt = shape
+    print(f"[edges] wide {shape}", flush=True)
+    w = Workload("wide", V=V, B=B, N=N, k=k, r=r, R=R, dtype=dt, peak="uniform", seed=9)
+    inp = make_inputs(w)
+    out = _run(w, inp)
+    reps = C.compare_batch(out, inp, k, N, label=f"wide {shape}")
+    assert all(rep["exact"] or rep["identical"] for rep in reps), reps

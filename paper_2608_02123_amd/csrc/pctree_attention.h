@@ -11,7 +11,7 @@ namespace pctree {
 
 // Work split of one call, a pure function of the shape and the CU count.
 struct AttnPlan {
-  int qblocks;      // 64-row query blocks per (request, key/value head)
+  int qblocks;      // 128-row query blocks per (request, key/value head)
   int nsplit;       // key-slot runs per query block (1: no merge pass)
   int split_keys;   // slots per run, a multiple of 64
   int blocks;       // workgroups of the attention kernel (XCD-grouped, padded)

@@ -8,12 +8,15 @@
 // Layout (bf16): q [R][N][Hq][D], k and v [R][Hkv][C][D], out [R][N][Hq][D];
 // query head h reads key/value head h / g, g = Hq / Hkv.
 //
-// One workgroup (4 waves of 32 rows) takes 128 query rows of one key/value
-// head, row rho = node * g + (h mod g), and a run of key slots (the whole
-// admitted range, or one split of it when there are too few workgroups to
-// fill the chip).  Key slots go through LDS 64 at a time (register-prefetched
-// one chunk ahead): K row-major, V transposed, shared by the four waves, with
-// a 64-bit window per tree node of which of the chunk's slots it admits.
+// One workgroup takes 128 query rows of one key/value head, row rho = node * g
+// + (h mod g), and a run of key slots (the whole admitted range, or one split
+// of it when there are too few workgroups to fill the chip).  Its eight waves
+// are two groups of four (32 rows each) that take the run's 64-slot chunks in
+// turn and join their results at the end, so that two waves share a SIMD and a
+// long request's chain of chunks is half as long.  K and V of a chunk go from
+// memory straight into LDS (no registers, no staging instructions), one chunk
+// ahead, both row-major with their 16-byte units permuted so that the fragment
+// reads touch all banks; V's fragments are read with the transposing LDS read.
 // Each wave owns two 16-row column tiles and computes, on bf16 MFMA 16x16x32
 // with fp32 accumulation (every K and V fragment read from LDS serves both
 // tiles),
@@ -22,9 +25,17 @@
 // with an online softmax in base 2 (one update per chunk).  The two K tiles of a pair take keys
 // {8c..8c+3} and {8c+4..8c+7} on row group c, so that every lane ends up with
 // the scores of 8 consecutive keys of its query row: exactly the B operand
-// of the second product, with no data movement between lanes.  Split runs
-// leave (max, sum, unnormalised output) per row in the workspace and a
-// second kernel merges them.
+// of the second product, with no data movement between lanes.
+//
+// With few workgroups and a cache of at most kDirectChunks chunks, a second
+// kernel gives each of a workgroup's eight waves its own chunks for 16 or 32
+// rows, and joins them in LDS; longer caches are split over workgroups, whose
+// runs leave (max, sum, unnormalised output) per row in the workspace for a
+// merging kernel.
+//
+// What bounds the first is instruction issue: staging through registers
+// (zeroing, transposing V by 16-bit stores) and the softmax took 460 vector
+// instructions per 64 MFMAs, now 250.
 #include "pctree.h"
 
 #include <hip/hip_runtime.h>
@@ -40,13 +51,13 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-constexpr int kThreads = 256;      // 4 waves
+constexpr int kGroups = 2;         // slot groups of a workgroup, 4 waves each
+constexpr int kGroupThreads = 256;
+constexpr int kThreads = kGroups * kGroupThreads;
 constexpr int kColTiles = 2;       // 16-row MFMA column tiles per wave
 constexpr int kRowsPerWave = 16 * kColTiles;
 constexpr int kRowsPerBlock = 4 * kRowsPerWave;  // query rows of one workgroup
 constexpr int kChunk = 64;         // key slots per LDS stage (two 32-slot halves)
-constexpr int kKPad = 8;           // bf16 padding of an LDS K row
-constexpr int kVPad = 8;           // bf16 padding of an LDS V^T row
 constexpr int kMaxSplits = 32;     // slot runs merged by one merge thread
 constexpr int kXcds = 8;           // L2 domains the dispatcher deals workgroups over
 constexpr int kMergeThreads = 256;
@@ -70,11 +81,52 @@ __device__ __forceinline__ f32x4 mfma_bf16(u32x4 a, u32x4 b, f32x4 c) {
                                                   __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
-// 16-byte group of K row `row` that holds d group `dg` in LDS.  Rows are
-// D + 8 bf16 long (a shift of 4 banks per row), and the fragment reads of a
-// 16-lane group touch rows {0..3, 8..11, 16..19, 24..27} (+ 4, + 32): rows 16
-// apart would share banks, so rows with bit 4 set swap d groups 4 apart.
-__device__ __forceinline__ int kswz(int row, int dg) { return dg ^ (((row >> 4) & 1) << 2); }
+// Permutation of the 16-byte units of a K or V row in LDS (an XOR of the unit
+// index).  A K fragment read takes one unit of the 16 rows {0..3, 8..11,
+// 16..19, 24..27} (+ 4, + 32); with 256-byte rows all of them start in one
+// bank, so the four row bits that vary choose among the 16 units (rows of 128
+// bytes alternate between two halves of the banks: three bits choose among
+// 8).  A V fragment read takes 32 bytes (two units) of four consecutive keys
+// per lane group: pairs of units are permuted by the key's low two bits and
+// its bit 3, all that fits the 8 pairs (or two of the three, D = 64).
+template <int D>
+__device__ __forceinline__ int k_unit(int row) {
+  return D == 128 ? (row & 3) | ((row >> 1) & 12) : ((row >> 1) & 1) | ((row >> 2) & 6);
+}
+template <int D>
+__device__ __forceinline__ int v_unit(int row) {
+  return D == 128 ? ((row & 3) << 1) | (row & 8) : (row & 2) | ((row >> 1) & 4);
+}
+
+// 16 bytes per lane from global memory straight into LDS (lane l's bytes at
+// lds + 16 l), counted in vmcnt: inline assembly, because the compiler would
+// order every later LDS read after it; wait_loads() and a barrier do.  `base`
+// is uniform, `off` the lane's byte offset.
+__device__ __forceinline__ void load_lds16(const void* base, uint32_t off, const void* lds) {
+  const uint32_t at = __builtin_amdgcn_readfirstlane(
+      (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)lds);
+  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, %2" ::"v"(off), "s"(at), "s"(base)
+               : "memory", "m0");
+}
+__device__ __forceinline__ void wait_loads() {
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+}
+// A workgroup barrier for LDS traffic.
+__device__ __forceinline__ void lds_barrier() {
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+  __builtin_amdgcn_s_barrier();
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+}
+
+// Transposing LDS read: in each 16 lanes, lanes 4 i .. 4 i + 3 address row i (16
+// consecutive 16-bit values), and lane l receives column l of rows 0 .. 3.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ u32x2 read_tr(const uint16_t* src) {
+  return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+      (__attribute__((address_space(3))) s16x4*)src));
+}
 
 // Low `n` bits set, n in [0, 64].
 __device__ __forceinline__ uint64_t low_bits(int n) {
@@ -104,16 +156,29 @@ struct Work {
   bool ok;
 };
 
-__device__ __forceinline__ Work work_of(const AttnArgs& a) {
+__device__ __forceinline__ Work work_of(const AttnArgs& a, int qblocks, int nsplit) {
   const int b = blockIdx.x;
   const int j = b / kXcds;
-  const int grp = (j / a.qblocks) * kXcds + b % kXcds;
+  const int grp = (j / qblocks) * kXcds + b % kXcds;
   Work w;
-  w.ok = grp < a.R * a.Hkv * a.nsplit;
-  w.qb = j % a.qblocks;
-  w.split = grp % a.nsplit;
-  w.kvh = grp / a.nsplit % a.Hkv;
-  w.r = grp / a.nsplit / a.Hkv;
+  w.ok = grp < a.R * a.Hkv * nsplit;
+  w.qb = j % qblocks;
+  w.split = grp % nsplit;
+  w.kvh = grp / nsplit % a.Hkv;
+  w.r = grp / nsplit / a.Hkv;
+  // Longest requests first (up to 64 requests, one per lane): the workgroups
+  // that start last, on the compute units that are free first, are then the
+  // shortest ones.
+  if (a.R > 1 && a.R <= 64 && w.ok) {
+    const int lane = threadIdx.x & 63;
+    const int len = lane < a.R ? req_range(a, min(lane, a.R - 1)).end : -1;
+    int rank = 0;
+    for (int i = 0; i < a.R; ++i) {
+      const int o = __builtin_amdgcn_readlane(len, i);
+      rank += o > len || (o == len && i < lane);
+    }
+    w.r = __builtin_ctzll(__ballot(rank == w.r));
+  }
   return w;
 }
 
@@ -133,10 +198,10 @@ __device__ __forceinline__ float row_max4(float v) {
 // Online softmax of one 16-row column tile over a 64-slot chunk.  s[h][t]
 // holds the raw scores q.k of half h, tile t (slots 32 h + 8 grp + 4 t + e);
 // `adm` has bit 8 h + i set when slot 32 h + 8 grp + i is admitted (ignored
-// when `all`).  The running maximum m is kept in raw units, which needs
-// scale > 0: the weights are 2^(scale log2(e) (s - m)).  Writes the weights
-// as bf16 B operands bp[h] and returns the factor the accumulated output must
-// be scaled by.
+// when `all`).  The running maximum m is kept in raw units, which
+// needs scale > 0: the weights are 2^(scale log2(e) (s - m)).  Writes the
+// weights as bf16 B operands bp[h] and returns the factor the accumulated
+// output must be scaled by.
 __device__ __forceinline__ float softmax_chunk(const f32x4 (&s)[2][2], uint32_t adm, bool all,
                                                float c, float& m, float& l, u32x4 (&bp)[2]) {
   float v[16];
@@ -154,17 +219,22 @@ __device__ __forceinline__ float softmax_chunk(const f32x4 (&s)[2][2], uint32_t 
   float cmax = v[0];
 #pragma unroll
   for (int i = 1; i < 16; ++i) cmax = fmaxf(cmax, v[i]);
-  const float mn = fmaxf(m, row_max4(cmax));
-  const float alpha = mn == m ? 1.0f : exp2_hw((m - mn) * c);  // m = -inf: 0
-  const float off = mn == kNegInf ? 0.0f : mn * c;  // nothing admitted yet: every weight 0
+  const float mx = row_max4(cmax);
+  float alpha = 1.0f;
+  if (__any(mx > m)) {
+    const float mn = fmaxf(m, mx);
+    alpha = mn == m ? 1.0f : exp2_hw((m - mn) * c);  // m = -inf: 0
+    m = mn;
+    l *= alpha;
+  }
+  const float off = m == kNegInf ? 0.0f : m * c;  // nothing admitted yet: every weight 0
   float ps = 0.0f;
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
     v[i] = exp2_hw(__builtin_fmaf(v[i], c, -off));
     ps += v[i];
   }
-  m = mn;
-  l = l * alpha + ps;
+  l += ps;
 #pragma unroll
   for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -172,22 +242,44 @@ __device__ __forceinline__ float softmax_chunk(const f32x4 (&s)[2][2], uint32_t 
   return alpha;
 }
 
-template <int D>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) void attn_kernel(AttnArgs a) {
-  constexpr int KS = D / 32;  // contraction steps of S = K Q^T
-  constexpr int DT = D / 16;  // 16-wide d tiles of O
-  constexpr int KROW = D + kKPad;
-  constexpr int VROW = kChunk + kVPad;
-  constexpr int DG = D / 8;   // 16-byte groups of a row
-  constexpr int CT = kColTiles;
-  __shared__ __attribute__((aligned(16))) uint16_t sK[kChunk * KROW];
-  __shared__ __attribute__((aligned(16))) uint16_t sV[D * VROW];
-  __shared__ uint64_t sWin[kRowsPerBlock];  // admitted slots of the chunk, per node
+// Admitted slots of the 64-slot chunk at c0 for a node with mask words mw (in
+// LDS), as the 16 bits of lane group grp: bits 8 h + i for slot 32 h + 8 grp + i.
+__device__ __forceinline__ uint32_t admitted(const AttnArgs& a, const ReqRange& rr,
+                                             const uint32_t* mw, int c0, int kend, int grp) {
+  const int j0 = c0 - rr.prefix;
+  const int wb = j0 >> 5, sh = j0 & 31;  // (floor)
+  const uint32_t w0 = wb >= 0 && wb < a.NW ? mw[wb] : 0u;
+  const uint32_t w1 = wb + 1 >= 0 && wb + 1 < a.NW ? mw[wb + 1] : 0u;
+  const uint32_t w2 = wb + 2 >= 0 && wb + 2 < a.NW ? mw[wb + 2] : 0u;
+  const uint64_t lo64 = ((uint64_t)w1 << 32) | w0;
+  const uint64_t tree = sh ? (lo64 >> sh) | ((uint64_t)w2 << (64 - sh)) : lo64;
+  const int np = min(max(-j0, 0), kChunk);
+  const uint64_t win =
+      (low_bits(np) | (tree & ~low_bits(np))) & low_bits(min(max(kend - c0, 0), kChunk));
+  return ((uint32_t)(win >> (8 * grp)) & 0xffu) | ((uint32_t)(win >> (32 + 8 * grp)) & 0xffu) << 8;
+}
 
-  const Work wk = work_of(a);
+template <int D>
+__global__ __launch_bounds__(kThreads) void attn_kernel(AttnArgs a) {
+  constexpr int KS = D / 32;   // contraction steps of S = K Q^T
+  constexpr int DT = D / 16;   // 16-wide d tiles of O
+  constexpr int UPR = D / 8;   // 16-byte units of a K or V row
+  constexpr int CT = kColTiles;
+  constexpr int TILE = kChunk * D;            // bf16 of a chunk's K (or V)
+  constexpr int IPW = kChunk * UPR / 64 / 4;  // load instructions per wave, chunk and tensor
+  // [group][buffer][K, V]
+  __shared__ __attribute__((aligned(16))) uint16_t sKV[kGroups][2][2][TILE];
+  __shared__ uint32_t sMask[kRowsPerBlock * (PCTREE_MAX_MASK_BUDGET / 32)];  // the nodes' mask rows
+  __shared__ float2 sML[kRowsPerBlock];  // the second group's row statistics
+  static_assert(kGroups == 2 && sizeof(sKV) >= kRowsPerBlock * D * sizeof(float),
+                "the second group's output fits the tiles");
+
+  const Work wk = work_of(a, a.qblocks, a.nsplit);
   if (!wk.ok) return;
   const int r = wk.r, kvh = wk.kvh, split = wk.split;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int group = __builtin_amdgcn_readfirstlane(threadIdx.x / kGroupThreads);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x % kGroupThreads / 64);
+  const int lane = threadIdx.x & 63;
   const int col = lane & 15, grp = lane >> 4;
 
   // this lane's query rows (MFMA column col of each tile): rho = node * g + (h mod g)
@@ -214,40 +306,39 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     for (int s = 0; s < KS; ++s) bq[c][s] = *(const u32x4*)(qrow + s * 32);
   }
 
-  // Staging maps.  K: thread -> d group st_dg of key rows st_row + 16 i.
-  // V: thread -> key pair (2 vp, 2 vp + 1) and d groups vdg + 8 j, so that
-  // the 64 lanes of a wave write 64 different LDS banks of the transposed
-  // tile (lane pairs 32 apart sit 8 d rows apart: 288 bytes, 8 banks + 32).
-  const int st_dg = tid & 15, st_row = tid >> 4;
-  const bool st_on = st_dg < DG;
-  const int vp = tid & 31, vdg = tid >> 5;
-  constexpr int VJ = DG / 8;  // V d groups per thread (1 or 2)
-  const size_t kvbase = ((size_t)r * a.Hkv + kvh) * a.C;
-  const uint16_t* kbase_p = a.k + kvbase * D + st_dg * 8;
-  const uint16_t* vbase_p = a.v + kvbase * D + vdg * 8;
-  u32x4 nk[4], nv[2 * VJ];
-  // raw loads of chunk c0 (slot addresses clamped into the cache; slots past
-  // the run are zeroed when staged)
-  auto fetch = [&](int c0) {
-    if (st_on) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        nk[i] = *(const u32x4*)(kbase_p + (size_t)min(c0 + st_row + 16 * i, a.C - 1) * D);
-    }
-    const size_t s0 = (size_t)min(c0 + 2 * vp, a.C - 1) * D;
-    const size_t s1 = (size_t)min(c0 + 2 * vp + 1, a.C - 1) * D;
-#pragma unroll
-    for (int j = 0; j < VJ; ++j) {
-      nv[2 * j] = *(const u32x4*)(vbase_p + s0 + 64 * j);
-      nv[2 * j + 1] = *(const u32x4*)(vbase_p + s1 + 64 * j);
-    }
-  };
-  const int kbeg = split * a.split_keys;
-  fetch(kbeg);  // kbeg < C by construction of the runs
-
   const ReqRange rr = req_range(a, r);
+  // the groups take the run's chunks in turn
+  const int kbeg = split * a.split_keys;
   const int kend = min(kbeg + a.split_keys, rr.end);
   if (a.nsplit > 1 && kbeg >= rr.end) return;  // empty run: the merge skips it
+
+  // A chunk's K and V into a buffer: instruction i of the wave fills LDS units
+  // 64 (IPW wave + i) ..; the slot's row and the unit it holds there.  Slots
+  // past the run repeat its last one (a finite value that weight 0 drops).
+  const size_t kvbase = ((size_t)r * a.Hkv + kvh) * a.C * D;
+  auto fetch = [&](int c0, int buf) __attribute__((always_inline)) {
+    const uint16_t* kb = a.k + kvbase + (size_t)c0 * D;
+    const uint16_t* vb = a.v + kvbase + (size_t)c0 * D;
+    const int last = kend - 1 - c0;
+#pragma unroll
+    for (int i = 0; i < IPW; ++i) {
+      const int u = (wave * IPW + i) * 64 + lane;
+      const int row = u / UPR, pos = u % UPR;
+      const uint32_t ro = (uint32_t)min(row, last) * (D * 2);
+      load_lds16(kb, ro + (uint32_t)(pos ^ k_unit<D>(row)) * 16,
+                 &sKV[group][buf][0][(wave * IPW + i) * 512]);
+      load_lds16(vb, ro + (uint32_t)(pos ^ v_unit<D>(row)) * 16,
+                 &sKV[group][buf][1][(wave * IPW + i) * 512]);
+    }
+  };
+  const int kfirst = kbeg + group * kChunk;
+  if (kfirst < kend) fetch(kfirst, 0);
+
+  // the mask rows of the block's nodes (bit j of a row is tree node j, at slot
+  // prefix + j)
+  const uint32_t* mrow_g = a.mask + ((size_t)r * a.N + n0) * a.NW;
+  for (int i = threadIdx.x; i < nn * a.NW; i += kThreads) sMask[i] = mrow_g[i];
+
   bool row_live[CT];
 #pragma unroll
   for (int c = 0; c < CT; ++c) {
@@ -257,22 +348,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
       for (int s = 0; s < KS; ++s) bq[c][s] = u32x4{0u, 0u, 0u, 0u};
     }
   }
-
-  // Admission windows: thread t < nn keeps, for node n0 + t, the three mask
-  // words that cover the chunk's tree slots (bit j of the mask row is tree
-  // node j, at slot prefix + j).
-  const uint32_t* mrow_g = a.mask + ((size_t)r * a.N + n0 + min(tid, nn - 1)) * a.NW;
-  uint32_t mw0 = 0, mw1 = 0, mw2 = 0;
-  auto fetch_mask = [&](int c0) {
-    mw0 = mw1 = mw2 = 0;
-    if (tid >= nn || c0 + kChunk <= rr.prefix || c0 >= kend) return;  // no tree slot
-    const int j0 = c0 - rr.prefix;
-    const int wb = j0 >= 0 ? j0 >> 5 : -((31 - j0) >> 5);  // floor(j0 / 32)
-    if (wb >= 0 && wb < a.NW) mw0 = mrow_g[wb];
-    if (wb + 1 >= 0 && wb + 1 < a.NW) mw1 = mrow_g[wb + 1];
-    if (wb + 2 >= 0 && wb + 2 < a.NW) mw2 = mrow_g[wb + 2];
-  };
-  fetch_mask(kbeg);
 
   f32x4 o[CT][DT];
   float m[CT], l[CT];
@@ -284,58 +359,20 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     for (int t = 0; t < DT; ++t) o[c][t] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
 
-  auto stage = [&](int c0) {
-    const u32x4 z = {0u, 0u, 0u, 0u};
-    if (st_on) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int row = st_row + 16 * i;
-        *(u32x4*)(sK + row * KROW + kswz(row, st_dg) * 8) = c0 + row < kend ? nk[i] : z;
-      }
-    }
-    const bool lo_ok = c0 + 2 * vp < kend, hi_ok = c0 + 2 * vp + 1 < kend;
-#pragma unroll
-    for (int j = 0; j < VJ; ++j) {
-      const u32x4 lo = lo_ok ? nv[2 * j] : z;
-      const u32x4 hi = hi_ok ? nv[2 * j + 1] : z;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        // d = 8 (vdg + 8 j) + 2e (low halves) and + 1 (high halves); keys 2 vp, + 1
-        uint16_t* dst = sV + ((vdg + 8 * j) * 8 + 2 * e) * VROW + 2 * vp;
-        *(uint32_t*)dst = (lo[e] & 0xffffu) | (hi[e] << 16);
-        *(uint32_t*)(dst + VROW) = (lo[e] >> 16) | (hi[e] & 0xffff0000u);
-      }
-    }
-    if (tid < nn) {
-      // bit i: slot c0 + i is admitted for node n0 + tid
-      uint64_t win = 0;
-      if (n0 + tid < rr.cnt) {
-        const int j0 = c0 - rr.prefix;
-        const int sh = j0 & 31;  // j0 - 32 floor(j0 / 32)
-        const uint64_t lo64 = ((uint64_t)mw1 << 32) | mw0;
-        const uint64_t tree = sh ? (lo64 >> sh) | ((uint64_t)mw2 << (64 - sh)) : lo64;
-        const int np = min(max(rr.prefix - c0, 0), kChunk);
-        win = (low_bits(np) | (tree & ~low_bits(np))) & low_bits(min(max(kend - c0, 0), kChunk));
-      }
-      sWin[tid] = win;
-    }
-  };
-
   // A-operand rows of an S^T tile pair: tile 0 holds keys 8c + e, tile 1 keys
   // 8c + 4 + e, for MFMA row 4c + e (c = col / 4, e = col % 4)
   const int krow0 = 8 * (col >> 2) + (col & 3);
 
-  for (int c0 = kbeg; c0 < kend; c0 += kChunk) {
-    __syncthreads();  // the previous chunk is no longer read
-    stage(c0);
-    __syncthreads();
-    if (c0 + kChunk < kend) {
-      fetch(c0 + kChunk);
-      fetch_mask(c0 + kChunk);
-    }
-    uint64_t win[CT];
-#pragma unroll
-    for (int c = 0; c < CT; ++c) win[c] = row_live[c] ? sWin[node[c] - n0] : 0ull;
+  // (the step's base chunk is the first group's; the second may have one less)
+  int buf = 0;
+  for (int cb = kbeg; cb < kend; cb += kGroups * kChunk, buf ^= 1) {
+    const int c0 = cb + group * kChunk;
+    wait_loads();
+    lds_barrier();  // the chunk is complete; the other buffer is no longer read
+    if (c0 >= kend) break;  // (the last step: no barrier of the loop follows)
+    if (c0 + kGroups * kChunk < kend) fetch(c0 + kGroups * kChunk, buf ^ 1);
+    const uint16_t* sK = sKV[group][buf][0];
+    const uint16_t* sV = sKV[group][buf][1];
     // every slot of the chunk admitted for every live row: no masking (rows
     // past the tree then take weights like the rest and are written as zeros)
     const bool full = c0 + kChunk <= min(kend, rr.prefix);
@@ -350,10 +387,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     for (int k = 0; k < KS; ++k) {
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        const int row0 = 32 * h + krow0;
-        const u32x4 a0 = *(const u32x4*)(sK + row0 * KROW + kswz(row0, 4 * k + grp) * 8);
-        const u32x4 a1 =
-            *(const u32x4*)(sK + (row0 + 4) * KROW + kswz(row0 + 4, 4 * k + grp) * 8);
+        // (rows 4 and 32 apart share their permutation)
+        const uint16_t* kr = sK + (32 * h + krow0) * D + ((4 * k + grp) ^ k_unit<D>(krow0)) * 8;
+        const u32x4 a0 = *(const u32x4*)kr;
+        const u32x4 a1 = *(const u32x4*)(kr + 4 * D);
 #pragma unroll
         for (int c = 0; c < CT; ++c) {
           sacc[c][h][0] = mfma_bf16(a0, bq[c][k], sacc[c][h][0]);
@@ -364,34 +401,65 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     u32x4 bp[CT][2];
 #pragma unroll
     for (int c = 0; c < CT; ++c) {
-      const uint32_t adm = (uint32_t)(win[c] >> (8 * grp)) & 0xffu |
-                           ((uint32_t)(win[c] >> (32 + 8 * grp)) & 0xffu) << 8;
+      const uint32_t adm =
+          !full && row_live[c]
+              ? admitted(a, rr, sMask + (node[c] - n0) * a.NW, c0, kend, grp)
+              : 0u;
       const float alpha =
           softmax_chunk(sacc[c], adm, full, a.scale_log2, m[c], l[c], bp[c]);
-      if (__any(alpha != 1.0f)) {  // rescale only when some row raised its max
+      if (__any(alpha != 1.0f)) {
 #pragma unroll
         for (int t = 0; t < DT; ++t) o[c][t] *= alpha;
       }
     }
-    const uint16_t* va = sV + col * VROW + 8 * grp;
+    // O^T += V^T P^T: lane (d = col, keys 8 grp .. + 7 of the half) from two
+    // transposing reads of four keys each
+    const int vkey = 8 * grp + (col >> 2);  // the key this lane addresses (of the first four)
 #pragma unroll
     for (int t = 0; t < DT; ++t) {
-      const u32x4 av0 = *(const u32x4*)(va + t * 16 * VROW);
-      const u32x4 av1 = *(const u32x4*)(va + t * 16 * VROW + 32);
 #pragma unroll
-      for (int c = 0; c < CT; ++c) {
-        o[c][t] = mfma_bf16(av0, bp[c][0], o[c][t]);
-        o[c][t] = mfma_bf16(av1, bp[c][1], o[c][t]);
+      for (int h = 0; h < 2; ++h) {
+        const uint16_t* vr = sV + (32 * h + vkey) * D +
+                             ((2 * t + ((col >> 1) & 1)) ^ v_unit<D>(vkey)) * 8 + (col & 1) * 4;
+        const u32x2 lo = read_tr(vr), hi = read_tr(vr + 4 * D);
+        const u32x4 av = {lo[0], lo[1], hi[0], hi[1]};
+#pragma unroll
+        for (int c = 0; c < CT; ++c) o[c][t] = mfma_bf16(av, bp[c][h], o[c][t]);
       }
     }
   }
 
+  // the row's sum over its four lane groups
 #pragma unroll
   for (int c = 0; c < CT; ++c) {
-    // the row's sum over its four lane groups
-    float lc = l[c];
-    lc += __shfl_xor(lc, 16, 64);
-    lc += __shfl_xor(lc, 32, 64);
+    l[c] += __shfl_xor(l[c], 16, 64);
+    l[c] += __shfl_xor(l[c], 32, 64);
+  }
+  // the second group's (max, sum, output) joins the first's, through the
+  // tiles' place in LDS
+  lds_barrier();
+  f32x4* sO = (f32x4*)sKV;
+  if (group == 1) {
+#pragma unroll
+    for (int c = 0; c < CT; ++c) {
+#pragma unroll
+      for (int t = 0; t < DT; ++t) sO[((wave * CT + c) * DT + t) * 64 + lane] = o[c][t];
+      if (grp == 0) sML[wave * kRowsPerWave + 16 * c + col] = make_float2(m[c], l[c]);
+    }
+  }
+  lds_barrier();
+  if (group == 1) return;
+#pragma unroll
+  for (int c = 0; c < CT; ++c) {
+    const float2 ml = sML[wave * kRowsPerWave + 16 * c + col];
+    const float mn = fmaxf(m[c], ml.x);
+    const float w0 = m[c] == mn ? 1.0f : exp2_hw((m[c] - mn) * a.scale_log2);
+    const float w1 = ml.x == mn ? 1.0f : exp2_hw((ml.x - mn) * a.scale_log2);
+    m[c] = mn;  // (both -inf, no admitted slot: weights 1 on zeros)
+    const float lc = l[c] * w0 + ml.y * w1;
+#pragma unroll
+    for (int t = 0; t < DT; ++t)
+      o[c][t] = o[c][t] * w0 + sO[((wave * CT + c) * DT + t) * 64 + lane] * w1;
     if (!row_in[c]) continue;
     const size_t qidx = ((size_t)r * a.N + node[c]) * a.Hq + hq[c];  // (request, node, head)
     if (a.nsplit == 1) {
@@ -415,6 +483,175 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
         a.part_ml[2 * prow + 1] = row_live[c] ? lc : 0.0f;
       }
     }
+  }
+}
+
+// Few workgroups, short caches: 16 CT rows of one (request, kv head) per
+// workgroup; wave w takes the chunks w, w + 8, ... on its own (K fragments
+// straight from memory into registers, V through its own LDS tile) and the
+// eight waves' results are joined in LDS, so that nothing goes through the
+// workspace and no second launch follows (which took 4 of the 15 us of a
+// one-request layer; its partials were twice the layer's own bytes).
+constexpr int kDirectWaves = 8;
+constexpr int kDirectChunks = 32;  // (four chunks per wave)
+
+template <int D, int CT>
+__global__ __launch_bounds__(kDirectWaves * 64) void attn_direct_kernel(AttnArgs a, int qblocks) {
+  constexpr int KS = D / 32, DT = D / 16, UPR = D / 8;
+  constexpr int ROWS = 16 * CT;
+  constexpr int TILE = kChunk * D;              // bf16 of a chunk's V
+  constexpr int INS = kChunk * UPR / 64;        // load instructions of a chunk's V
+  constexpr int PART = CT * DT * 64;            // f32x4 of a wave's output
+  __shared__ __attribute__((aligned(16))) uint16_t sV[kDirectWaves][TILE];
+  __shared__ uint32_t sMask[ROWS * (PCTREE_MAX_MASK_BUDGET / 32)];
+  __shared__ float2 sML[kDirectWaves][ROWS];
+  static_assert(sizeof(uint16_t) * TILE >= PART * sizeof(f32x4), "a wave's output fits its V tile");
+
+  const Work wk = work_of(a, qblocks, 1);
+  if (!wk.ok) return;
+  const int r = wk.r, kvh = wk.kvh;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x & 63;
+  const int col = lane & 15, grp = lane >> 4;
+  const int rows_kv = a.N * a.g;
+  const int n0 = wk.qb * ROWS / a.g;
+  const int nn = min((wk.qb * ROWS + ROWS - 1) / a.g - n0 + 1, a.N - n0);
+  bool row_in[CT];
+  int node[CT], hq[CT];
+  u32x4 bq[CT][KS];
+#pragma unroll
+  for (int c = 0; c < CT; ++c) {
+    const int rho = wk.qb * ROWS + 16 * c + col;
+    row_in[c] = rho < rows_kv;
+    node[c] = row_in[c] ? rho / a.g : 0;
+    hq[c] = kvh * a.g + (row_in[c] ? rho % a.g : 0);
+    const uint16_t* qrow = a.q + (((size_t)r * a.N + node[c]) * a.Hq + hq[c]) * D + grp * 8;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) bq[c][s] = *(const u32x4*)(qrow + s * 32);
+  }
+  const ReqRange rr = req_range(a, r);
+  const int kend = rr.end;
+  const size_t kvbase = ((size_t)r * a.Hkv + kvh) * a.C * D;
+  const uint32_t* mrow_g = a.mask + ((size_t)r * a.N + n0) * a.NW;
+  for (int i = threadIdx.x; i < nn * a.NW; i += kDirectWaves * 64) sMask[i] = mrow_g[i];
+  bool row_live[CT];
+  f32x4 o[CT][DT];
+  float m[CT], l[CT];
+#pragma unroll
+  for (int c = 0; c < CT; ++c) {
+    row_live[c] = row_in[c] && node[c] < rr.cnt;
+    if (!row_live[c]) {
+#pragma unroll
+      for (int s = 0; s < KS; ++s) bq[c][s] = u32x4{0u, 0u, 0u, 0u};
+    }
+    m[c] = kNegInf;
+    l[c] = 0.0f;
+#pragma unroll
+    for (int t = 0; t < DT; ++t) o[c][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  lds_barrier();  // the mask rows
+  const int krow0 = 8 * (col >> 2) + (col & 3);
+  const int vkey = 8 * grp + (col >> 2);
+  for (int c0 = wave * kChunk; c0 < kend; c0 += kDirectWaves * kChunk) {
+    // (slots past the range repeat its last one, which weight 0 drops)
+    const int last = kend - 1 - c0;
+    const uint16_t* kb = a.k + kvbase + (size_t)c0 * D;
+    const uint16_t* vb = a.v + kvbase + (size_t)c0 * D;
+#pragma unroll
+    for (int i = 0; i < INS; ++i) {
+      const int u = i * 64 + lane, row = u / UPR, pos = u % UPR;
+      load_lds16(vb, (uint32_t)min(row, last) * (D * 2) + (uint32_t)(pos ^ v_unit<D>(row)) * 16,
+                 &sV[wave][i * 512]);
+    }
+    u32x4 kf[2][2][KS];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const uint16_t* kr = kb + (size_t)min(32 * h + krow0 + 4 * t, last) * D + grp * 8;
+#pragma unroll
+        for (int k = 0; k < KS; ++k) kf[h][t][k] = *(const u32x4*)(kr + 32 * k);
+      }
+    f32x4 sacc[CT][2][2];
+#pragma unroll
+    for (int c = 0; c < CT; ++c)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) sacc[c][h][0] = sacc[c][h][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < KS; ++k)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+          sacc[c][h][0] = mfma_bf16(kf[h][0][k], bq[c][k], sacc[c][h][0]);
+          sacc[c][h][1] = mfma_bf16(kf[h][1][k], bq[c][k], sacc[c][h][1]);
+        }
+    const bool full = c0 + kChunk <= min(kend, rr.prefix);
+    u32x4 bp[CT][2];
+#pragma unroll
+    for (int c = 0; c < CT; ++c) {
+      const uint32_t adm = !full && row_live[c]
+                               ? admitted(a, rr, sMask + (node[c] - n0) * a.NW, c0, kend, grp)
+                               : 0u;
+      const float alpha = softmax_chunk(sacc[c], adm, full, a.scale_log2, m[c], l[c], bp[c]);
+      if (__any(alpha != 1.0f)) {
+#pragma unroll
+        for (int t = 0; t < DT; ++t) o[c][t] *= alpha;
+      }
+    }
+    wait_loads();
+#pragma unroll
+    for (int t = 0; t < DT; ++t)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const uint16_t* vr = sV[wave] + (32 * h + vkey) * D +
+                             ((2 * t + ((col >> 1) & 1)) ^ v_unit<D>(vkey)) * 8 + (col & 1) * 4;
+        const u32x2 lo = read_tr(vr), hi = read_tr(vr + 4 * D);
+        const u32x4 av = {lo[0], lo[1], hi[0], hi[1]};
+#pragma unroll
+        for (int c = 0; c < CT; ++c) o[c][t] = mfma_bf16(av, bp[c][h], o[c][t]);
+      }
+    // (the tile's reads are back before the next chunk's loads overwrite it)
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  }
+  // the waves' results, each in its own V tile's place
+  f32x4* sO = (f32x4*)sV[wave];
+#pragma unroll
+  for (int c = 0; c < CT; ++c) {
+    l[c] += __shfl_xor(l[c], 16, 64);
+    l[c] += __shfl_xor(l[c], 32, 64);
+    if (grp == 0) sML[wave][16 * c + col] = make_float2(m[c], l[c]);
+#pragma unroll
+    for (int t = 0; t < DT; ++t) sO[(c * DT + t) * 64 + lane] = o[c][t];
+  }
+  lds_barrier();
+  for (int e = threadIdx.x; e < PART; e += kDirectWaves * 64) {
+    const int ct = e / 64, c = ct / DT, t = ct % DT;  // (e % 64 == lane)
+    const int rho = wk.qb * ROWS + 16 * c + col;
+    if (rho >= rows_kv) continue;
+    float M = kNegInf;
+    float2 ml[kDirectWaves];
+#pragma unroll
+    for (int w = 0; w < kDirectWaves; ++w) {
+      ml[w] = sML[w][16 * c + col];
+      M = fmaxf(M, ml[w].x);
+    }
+    float L = 0.0f;
+    f32x4 O = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < kDirectWaves; ++w) {
+      const float wt = ml[w].x == kNegInf ? 0.0f : exp2_hw((ml[w].x - M) * a.scale_log2);
+      L += wt * ml[w].y;
+      O += ((const f32x4*)sV[w])[e] * wt;
+    }
+    const int nd = rho / a.g;
+    const float inv = nd < rr.cnt && L > 0.0f ? 1.0f / L : 0.0f;
+    u32x2 wv;
+    wv[0] = pack_bf16(O[0] * inv, O[1] * inv);
+    wv[1] = pack_bf16(O[2] * inv, O[3] * inv);
+    *(u32x2*)(a.out + (((size_t)r * a.N + nd) * a.Hq + kvh * a.g + rho % a.g) * D + t * 16 +
+              4 * grp) = wv;
   }
 }
 
@@ -500,7 +737,27 @@ AttnPlan plan_attention(int R, int N, int Hq, int Hkv, int D, int C, int cus) {
   return p;
 }
 
+namespace {
+
+template <int D, int CT>
+hipError_t launch_direct(const AttnArgs& a, int qblocks, hipStream_t stream) {
+  const unsigned groups = (unsigned)((a.R * a.Hkv + kXcds - 1) / kXcds * kXcds);
+  attn_direct_kernel<D, CT><<<groups * qblocks, kDirectWaves * 64, 0, stream>>>(a, qblocks);
+  return hipGetLastError();
+}
+
+}  // namespace
+
 hipError_t launch_attention(AttnArgs a, int blocks, int D, hipStream_t stream) {
+  // Layers that would be split (fewer than 128 workgroups of 128 rows) take
+  // the direct kernel while each of its waves has at most four chunks: 16 rows
+  // per workgroup up to one workgroup per compute unit, 32 beyond.
+  if (a.nsplit > 1 && (a.C + kChunk - 1) / kChunk <= kDirectChunks) {
+    const int rows = a.N * a.g, q16 = (rows + 15) / 16, q32 = (rows + 31) / 32;
+    if ((long long)a.R * a.Hkv * q16 <= 256)
+      return D == 128 ? launch_direct<128, 1>(a, q16, stream) : launch_direct<64, 1>(a, q16, stream);
+    return D == 128 ? launch_direct<128, 2>(a, q32, stream) : launch_direct<64, 2>(a, q32, stream);
+  }
   if (D == 128)
     attn_kernel<128><<<blocks, kThreads, 0, stream>>>(a);
   else

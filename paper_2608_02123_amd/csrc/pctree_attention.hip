@@ -27,7 +27,8 @@
 // the scores of 8 consecutive keys of its query row: exactly the B operand
 // of the second product, with no data movement between lanes.
 //
-// With few workgroups and a cache of at most kDirectChunks chunks, a second
+// With few workgroups and a cache of at most kDirectChunks chunks (three per
+// wave), a second
 // kernel gives each of a workgroup's eight waves its own chunks for 16 or 32
 // rows, and joins them in LDS; longer caches are split over workgroups, whose
 // runs leave (max, sum, unnormalised output) per row in the workspace for a
@@ -493,7 +494,7 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnArgs a) {
 // workspace and no second launch follows (which took 4 of the 15 us of a
 // one-request layer; its partials were twice the layer's own bytes).
 constexpr int kDirectWaves = 8;
-constexpr int kDirectChunks = 32;  // (four chunks per wave)
+constexpr int kDirectChunks = 24;  // (three chunks per wave)
 
 template <int D, int CT>
 __global__ __launch_bounds__(kDirectWaves * 64) void attn_direct_kernel(AttnArgs a, int qblocks) {
@@ -750,13 +751,21 @@ hipError_t launch_direct(const AttnArgs& a, int qblocks, hipStream_t stream) {
 
 hipError_t launch_attention(AttnArgs a, int blocks, int D, hipStream_t stream) {
   // Layers that would be split (fewer than 128 workgroups of 128 rows) take
-  // the direct kernel while each of its waves has at most four chunks: 16 rows
-  // per workgroup up to one workgroup per compute unit, 32 beyond.
-  if (a.nsplit > 1 && (a.C + kChunk - 1) / kChunk <= kDirectChunks) {
+  // the direct kernel while each wave has at most three chunks and all
+  // workgroups fit one to a compute unit, with 16 rows each or else 32; with
+  // one chunk per wave also at two per unit.  Against split runs, in us
+  // (heads of 128; N rows of nodes, 4 or 5 query heads to a key/value head):
+  //   one request, N 64:    C 256 7.0 / 13.7,  C 1536 17.6 / 19.1,  C 2048 22.1 / 19.9
+  //   one request, N 128:   C 256 9.2 / 16.6,  C 1536 20.3 / 25.9
+  //   two requests, N 128:  C 256 17.7 / 20.9, C 512 22.3 / 23.5,   C 1088 33.1 / 27.5
+  const int chunks = (a.C + kChunk - 1) / kChunk;
+  if (a.nsplit > 1 && chunks <= kDirectChunks) {
     const int rows = a.N * a.g, q16 = (rows + 15) / 16, q32 = (rows + 31) / 32;
-    if ((long long)a.R * a.Hkv * q16 <= 256)
+    const long long heads = (long long)a.R * a.Hkv;
+    if (heads * q16 <= 256)
       return D == 128 ? launch_direct<128, 1>(a, q16, stream) : launch_direct<64, 1>(a, q16, stream);
-    return D == 128 ? launch_direct<128, 2>(a, q32, stream) : launch_direct<64, 2>(a, q32, stream);
+    if (heads * q32 <= 256 || chunks <= kDirectWaves)
+      return D == 128 ? launch_direct<128, 2>(a, q32, stream) : launch_direct<64, 2>(a, q32, stream);
   }
   if (D == 128)
     attn_kernel<128><<<blocks, kThreads, 0, stream>>>(a);

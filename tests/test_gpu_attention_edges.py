@@ -1,6 +1,6 @@
 """Tree attention at the edges of its work splits, against the float64 oracle.
 
-The direct kernel (few workgroups, at most 32 chunks of 64 slots, eight waves
+The direct kernel (few workgroups, at most 24 chunks of 64 slots, eight waves
 with chunks of their own): admitted ranges that end one short of, on and one
 past a chunk, a round of eight chunks and the largest cache; 15, 16, 17 and 33
 rows; requests without slots.  The split runs and their merge (longer caches).
@@ -24,7 +24,10 @@ CASES = [
     ("one past a chunk", 17, 2, 2, 128, [48], [17], None),
     ("eight chunks", 11, 6, 2, 64, [501], [11], 600),
     ("eight chunks and a slot", 11, 6, 2, 128, [502], [11], 600),
-    ("the largest direct cache", 45, 28, 4, 128, [2003], [45], 2048),
+    ("the largest direct cache", 45, 28, 4, 128, [1491], [45], 1536),
+    ("one slot more: split runs", 45, 28, 4, 128, [1492], [45], 1537),
+    ("two workgroups per unit", 128, 40, 8, 64, [300, 130], [128, 120], 512),
+    ("too many workgroups: split runs", 128, 40, 8, 64, [480, 130], [128, 120], 640),
     ("32 rows per workgroup", 128, 40, 8, 128, [100, 7], [128, 90], 300),
     ("requests without slots", 20, 8, 2, 64, [0, 30, 0], [0, 0, 20], 60),
     ("split runs", 40, 8, 2, 128, [2100], [40], None),

@@ -1405,7 +1405,7 @@ __device__ __forceinline__ float word_value(uint64_t w) {
 // The plan as one stage uses it: its scalars are opaque to the compiler, so
 // that comparisons and addresses made from them are made anew in every stage.
 // Hoisted out of the stage loop they overflow the scalar registers, and the
-// reloads cost more than the few operations (0.6 us of a stage).
+// reloads cost more than the few operations (0.2 us of an 8.6 us stage).
 // detach_plan() is called once before the loop: the launch arguments arrive in
 // blocks of 16 scalar registers, which are kept and spilled whole while any
 // field of theirs is in use.
@@ -2097,8 +2097,9 @@ struct MergeShared {
 // every stage, four waves per row, one slice per lane.  The row's k' best lie
 // among the record keys at or above the k'-th largest of the slice groups'
 // best keys (those are k' distinct keys), a handful, which are ranked by
-// counting: against k' pops of the wave-wide maximum over four slices per lane
-// this took 0.6 us instead of 1.9 us.  Only if a slice gave up all of its
+// counting, where the same by k' pops of a wave-wide maximum is a chain of k'
+// times about 150 cycles.  From a row's last record to its published words it
+// takes 1.5 to 1.9 us (7 rows of 8 children, 240 slices, by stage stamps).  Only if a slice gave up all of its
 // record keys, its full list (and those of the other slices that gave a key)
 // settles the row.
 __device__ __forceinline__ void merge_block(const Plan& pl, FrontShared& fs, MergeShared& ms, int m) {
@@ -3744,6 +3745,11 @@ hipError_t launch_round(const Plan& p0, hipStream_t st) {
     int target = std::max(1, std::min(di.cus - others, kRoundSlicesMax));
     if (dbg.round_slices > 0) target = std::min(target, dbg.round_slices);
     p.tiles_per_slice = (p.ntiles + target - 1) / target;
+    // Small vocabularies: with at most as many children as a record holds, one
+    // tile per wave (fewer workgroups to hear from: chains at V 1874 42.1 -> 39.4
+    // us, at V 3646 for eight requests 51.8 -> 50.2); with more, one tile per
+    // slice, so that a slice seldom holds more of a row's best than its record.
+    if (p.kk <= kHeadKeys) p.tiles_per_slice = std::max(p.tiles_per_slice, kRoundWaves);
     p.G = (p.ntiles + p.tiles_per_slice - 1) / p.tiles_per_slice;
     // dynamic LDS: the frontier's head input and logits, then as many resident
     // W tiles as fit; the mergers' and keepers' state in its place there

@@ -22,13 +22,12 @@
 // tiles),
 //   S^T = K Q^T   (a 32-key x 16-row tile pair, contraction over D), then
 //   O^T += V^T P^T (D x 16 rows, contraction over the 32 keys),
-// with an online softmax in base 2 (one update per chunk).  The two K tiles of a pair take keys
-// {8c..8c+3} and {8c+4..8c+7} on row group c, so that every lane ends up with
-// the scores of 8 consecutive keys of its query row: exactly the B operand
-// of the second product, with no data movement between lanes.
+// with an online softmax in base 2 (one update per chunk).  The two K tiles of
+// a pair take keys {8c..8c+3} and {8c+4..8c+7} on row group c, so that every
+// lane ends up with the scores of 8 consecutive keys of its query row: exactly
+// the B operand of the second product, with no data movement between lanes.
 //
-// With few workgroups and a cache of at most kDirectChunks chunks (three per
-// wave), a second
+// With few workgroups and a cache of at most kDirectChunks chunks, a second
 // kernel gives each of a workgroup's eight waves its own chunks for 16 or 32
 // rows, and joins them in LDS; longer caches are split over workgroups, whose
 // runs leave (max, sum, unnormalised output) per row in the workspace for a

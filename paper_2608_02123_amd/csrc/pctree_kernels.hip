@@ -2099,9 +2099,9 @@ struct MergeShared {
 // best keys (those are k' distinct keys), a handful, which are ranked by
 // counting, where the same by k' pops of a wave-wide maximum is a chain of k'
 // times about 150 cycles.  From a row's last record to its published words it
-// takes 1.5 to 1.9 us (7 rows of 8 children, 240 slices, by stage stamps).  Only if a slice gave up all of its
-// record keys, its full list (and those of the other slices that gave a key)
-// settles the row.
+// takes 1.5 to 1.9 us (7 rows of 8 children, 240 slices, by stage stamps).
+// Only if a slice gave up all of its record keys, its full list (and those of
+// the other slices that gave a key) settles the row.
 __device__ __forceinline__ void merge_block(const Plan& pl, FrontShared& fs, MergeShared& ms, int m) {
   const Plan p0 = detach_plan(pl);
   const int tid = threadIdx.x;

@@ -42,6 +42,7 @@
 #include <stdint.h>
 
 #include "pctree_attention.h"
+#include "pctree_lds.h"
 
 namespace pctree {
 namespace {
@@ -98,16 +99,7 @@ __device__ __forceinline__ int v_unit(int row) {
   return D == 128 ? ((row & 3) << 1) | (row & 8) : (row & 2) | ((row >> 1) & 4);
 }
 
-// 16 bytes per lane from global memory straight into LDS (lane l's bytes at
-// lds + 16 l), counted in vmcnt: inline assembly, because the compiler would
-// order every later LDS read after it; wait_loads() and a barrier do.  `base`
-// is uniform, `off` the lane's byte offset.
-__device__ __forceinline__ void load_lds16(const void* base, uint32_t off, const void* lds) {
-  const uint32_t at = __builtin_amdgcn_readfirstlane(
-      (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)lds);
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, %2" ::"v"(off), "s"(at), "s"(base)
-               : "memory", "m0");
-}
+// Every vector-memory load of the wave has landed, those into LDS among them.
 __device__ __forceinline__ void wait_loads() {
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
   __atomic_signal_fence(__ATOMIC_SEQ_CST);

@@ -28,6 +28,7 @@
 //                                         (score desc, depth asc, token asc, slot asc)
 // where ord() maps a float onto an unsigned integer of the same order (-0 -> +0).
 #include "pctree.h"
+#include "pctree_lds.h"
 #include "pctree_plan.h"
 
 #include <float.h>
@@ -1308,20 +1309,6 @@ __device__ __forceinline__ void abort_outputs(const Plan& p, int req) {
     for (int e = threadIdx.x; e < nw; e += blockDim.x) p.o_mask[(size_t)req * nw + e] = 0u;
   }
   if (threadIdx.x == 0) p.o_count[req] = -1;
-}
-
-// 16 bytes per lane from global memory straight into LDS (lane l's bytes at
-// lds_dst + 16 l), counted in vmcnt like any vector-memory load.  Issued as
-// inline assembly: the compiler does not see the LDS write, so it does not
-// make later LDS reads wait for every load in flight (it cannot tell ring
-// slots apart); the kernel orders them itself with wait_vmcnt and a
-// barrier.  M0 holds the LDS base; nothing else in the kernels that use it
-// keeps a value in M0 across it.
-__device__ __forceinline__ void load_lds16(const void* src, const void* lds_dst) {
-  const uint32_t base = __builtin_amdgcn_readfirstlane(
-      (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)lds_dst);
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(base)
-               : "memory", "m0");
 }
 
 // s_waitcnt with only the vector-memory count limited (gfx9 encoding:

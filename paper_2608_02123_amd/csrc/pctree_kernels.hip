@@ -2201,7 +2201,10 @@ __device__ __forceinline__ void merge_block(const Plan& pl, FrontShared& fs, Mer
     float S = wm.y * exp2_raw((wm.x - M) * kLog2e);
     S += permf<kXor1>(S);
     S += permf<kXor2>(S);
-    const float lse = M + logf(S);
+    // one lane's sum for the row: the products above may be fused into the
+    // first addition, which rounds differently on either side of a pair, and
+    // which lane publishes a child depends on the order the waves arrive in
+    const float lse = M + logf(__uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(S))));
     const float parent = p.mode == 0 && d > 0 ? fs.score[row] : 0.0f;
     uint64_t* out = cand_words(p, d) + row * kk;
     auto publish = [&](int rank, uint64_t key) __attribute__((always_inline)) {

@@ -125,3 +125,22 @@ def test_wide_rows_at_any_alignment(shape):
     out = _run(w, inp)
     reps = C.compare_batch(out, inp, k, N, label=f"wide {shape}")
     assert all(rep["exact"] or rep["identical"] for rep in reps), reps
+
+
+@pytest.mark.parametrize("k,R,dt", [(8, 2, "f32"), (4, 2, "bf16"), (2, 4, "f32"), (16, 1, "bf16")])
+def test_rounds_repeat_bit_for_bit(k, R, dt):
+    """No output depends on the order in which workgroups and waves arrive."""
+    print(f"[edges] repeats k={k} R={R} {dt}", flush=True)
+    w = Workload("rep", V=32000, B=8, N=250, k=k, r=128, R=R, dtype=dt, peak="decay", seed=11)
+    dev = P.device_inputs(make_inputs(w))
+    b = P.TreeBuilder(w.V, w.B, w.N, w.k, w.r, w.R, P.BF16 if dt == "bf16" else P.F32, mask=True,
+                      trace=True)
+    g = torch.Generator(device="cuda").manual_seed(12)
+    for draw in range(12):
+        dev["L"].normal_(0.0, 3.0, generator=g)
+        ref = {n: t.clone() for n, t in b.run(**dev, check=True).items()}
+        for i in range(8):
+            out = b.run(**dev)
+            torch.cuda.synchronize()
+            for n, t in ref.items():
+                assert torch.equal(out[n], t), f"draw {draw} run {i}: {n} differs"

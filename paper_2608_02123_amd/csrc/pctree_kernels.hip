@@ -1933,6 +1933,9 @@ __device__ __forceinline__ void stream_block(const Plan& pl, FrontShared& fs, Ro
         const uint32_t om3 = all_max<3>(gt);
         // (0 when fewer groups hold a logit, or they tie: all logits pass)
         const float t3 = om3 <= f32_ord(-FLT_MAX) ? -FLT_MAX : f32_unord(om3);
+        // (finite, so that logits of -inf, masked tokens, have weight 0 also
+        // where a slice holds nothing else)
+        M = fmaxf(M, -FLT_MAX);
         if (b > 0) M = fmaxf(M, ms.x);
         float s = 0.0f;
 #pragma unroll
@@ -1948,13 +1951,15 @@ __device__ __forceinline__ void stream_block(const Plan& pl, FrontShared& fs, Ro
           __hip_atomic_store(at, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         };
         const uint64_t sumw = ((uint64_t)p.tag << 32) | __float_as_uint(s);
+        const int nb = min(nvalid - b * kZTiles * kTile, kZTiles * kTile);  // tokens of the batch
         bool slow = false;
         if (nbatch == 1) {
           // the record: the keys at or above t3, mostly one per lane
           const bool c = lm >= t3;
           const uint64_t cm = __ballot(c);
+          const int need = min(kHeadKeys, nb);
           int n = __popcll(cm);
-          if (n <= 8 && !__any(lm2 >= t3)) {
+          if (n >= need && n <= 8 && !__any(lm2 >= t3)) {
             int li = kZPer - 1;
 #pragma unroll
             for (int i = kZPer - 2; i >= 0; --i) li = v[i] == lm ? i : li;
@@ -1970,9 +1975,10 @@ __device__ __forceinline__ void stream_block(const Plan& pl, FrontShared& fs, Ro
             const int rank = cand_rank(cb, 1, key);
             if (c && rank < kHeadKeys) put(rec + rank * kSlicesMax, key | p.tag);
           } else {
-            n = row_cands(v, t3, tb, step, cb, 0, 0);
-            slow = n < 0;
-            for (int e = lane; e < n; e += 64) {
+            // (groups that tie in a whole wave of tokens: more candidates than fit)
+            n = om3 != 0 || nb <= 64 ? row_cands(v, t3, tb, step, cb, 0, 0) : -1;
+            slow = n < need;
+            for (int e = lane; !slow && e < n; e += 64) {
               const uint64_t key = cb[e];
               const int rank = cand_rank(cb, n, key);
               if (rank < kHeadKeys) put(rec + rank * kSlicesMax, key | p.tag);
@@ -1983,16 +1989,44 @@ __device__ __forceinline__ void stream_block(const Plan& pl, FrontShared& fs, Ro
             if (lane == 63) put(rec + kHeadKeys * kSlicesMax, sumw);
           }
         }
-        if (!slow && (nbatch > 1 || kk > kHeadKeys)) {
-          // the list, off the critical path
-          // (the least group's best has at least k' keys at or above it; a few
-          // bisections towards the row's maximum leave few more)
-          uint32_t gm = ~(kk > 8 ? g4 : g8);
+        // the least of the lane groups' bests: at least k' keys (and a record's
+        // worth) are at or above it
+        auto least_group = [&](uint32_t o4, uint32_t o8) __attribute__((always_inline)) {
+          uint32_t gm = ~(kk > 8 ? o4 : o8);
           if (kk > 8) gm = max(gm, perm<kHalfMirror>(gm));
           gm = max(gm, perm<kMirror>(gm));
           auto mx = [](uint32_t x, uint32_t y) { return max(x, y); };
-          gm = ~swap_op<32>(swap_op<16>(gm, mx), mx);
-          uint32_t lo = __builtin_amdgcn_readfirstlane(gm);
+          return (uint32_t)__builtin_amdgcn_readfirstlane(~swap_op<32>(swap_op<16>(gm, mx), mx));
+        };
+        // the candidates' m best in order, one per lane (rank[q]: of entry lane + 64 q)
+        auto in_order = [&](const uint64_t (&keys)[2], const int (&rank)[2], int m)
+                            __attribute__((always_inline)) {
+          __builtin_amdgcn_wave_barrier();
+          __atomic_signal_fence(__ATOMIC_SEQ_CST);
+          if (lane < kNarrowRows) cb[lane] = 0;
+          __builtin_amdgcn_wave_barrier();
+          __atomic_signal_fence(__ATOMIC_SEQ_CST);
+#pragma unroll
+          for (int q = 0; q < 2; ++q)
+            if (rank[q] < m) cb[rank[q]] = keys[q];
+          __builtin_amdgcn_wave_barrier();
+          __atomic_signal_fence(__ATOMIC_SEQ_CST);
+          return lane < m ? cb[lane] : 0ull;
+        };
+        auto ranked = [&](int n, uint64_t (&keys)[2], int (&rank)[2]) __attribute__((always_inline)) {
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {
+            const int e = lane + 64 * q;
+            keys[q] = e < n ? cb[e] : 0;
+            rank[q] = kNarrowRows;
+            if (64 * q < n) rank[q] = e < n ? cand_rank(cb, n, keys[q]) : kNarrowRows;
+          }
+        };
+        if (!slow && (nbatch > 1 || kk > kHeadKeys)) {
+          // the list, off the critical path
+          // (a few bisections from the least group's best towards the row's
+          // maximum leave few more than k' keys)
+          uint32_t lo = least_group(g4, g8);
           uint32_t hi = __builtin_amdgcn_readfirstlane(om);
 #pragma unroll 1
           for (int it = 0; it < 12 && lo < hi; ++it) {
@@ -2007,54 +2041,93 @@ __device__ __forceinline__ void stream_block(const Plan& pl, FrontShared& fs, Ro
           }
           const float tl = lo <= f32_ord(-FLT_MAX) ? -FLT_MAX : f32_unord(lo);
           const int n = row_cands(v, tl, tb, step, cb, carried, b > 0 ? kk : 0);
-          slow = n < 0;
+          slow = n < min(kk, nb) + (b > 0 ? kk : 0);
           if (!slow) {
             uint64_t keys[2];
             int rank[2];
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-              const int e = lane + 64 * q;
-              keys[q] = e < n ? cb[e] : 0;
-              rank[q] = e < n ? cand_rank(cb, n, keys[q]) : kNarrowRows;
-            }
+            ranked(n, keys, rank);
             if (nbatch == 1) {
 #pragma unroll
               for (int q = 0; q < 2; ++q)
                 if (rank[q] < p.kmax) put(list + rank[q], keys[q] | p.tag);
               if (lane >= n && lane < p.kmax) put(list + lane, p.tag);
             } else {
-              __builtin_amdgcn_wave_barrier();
-              __atomic_signal_fence(__ATOMIC_SEQ_CST);
-              if (lane < kNarrowRows) cb[lane] = 0;
-              __builtin_amdgcn_wave_barrier();
-              __atomic_signal_fence(__ATOMIC_SEQ_CST);
-#pragma unroll
-              for (int q = 0; q < 2; ++q)
-                if (rank[q] < kk) cb[rank[q]] = keys[q];
-              __builtin_amdgcn_wave_barrier();
-              __atomic_signal_fence(__ATOMIC_SEQ_CST);
-              lkey = lane < kk ? cb[lane] : 0;
+              lkey = in_order(keys, rank, kk);
             }
           }
         }
-        if (slow) {
-          // many equal logits: the best key below the last one, over and over
-          const int req = P == 1 ? row : div_kk(p, row);
-      const char* lrow = (const char*)p.L + ((size_t)req * p.B + d) * p.V * ESZ;
-          uint64_t prev = ~0ull;
-          for (int it = 0; it < max(kk, kHeadKeys); ++it) {
-            uint64_t top = carried < prev ? carried : 0;
-#pragma unroll 1
-            for (int i = 0; i < kZPer && i * 64 < left; ++i) {
-              const float z = p.mode == 2 ? 0.0f : zb[row * kZStride + i * 64 + lane];
-              const int tok = tb + i * step;
-              const uint64_t key =
-                  child_key(z + raw_to_f32<DT>(load_raw<DT>(lrow, (size_t)tok)), tok);
-              top = key < prev && key > top ? key : top;
-            }
-            prev = wave_max_u64(top);
-            if (lane == it) lkey = prev;
+        if (__builtin_expect(slow, 0)) {
+          // Many equal logits (masked vocabularies), or fewer above -FLT_MAX than
+          // the row needs (masked with -inf; a NaN counts as -inf here): the
+          // best `want` are the logits above T and the first of those equal to
+          // T, T being the least group's best or, if too many exceed that, the
+          // want-th best value.  The tokens of v[i] ascend with (i, lane), so
+          // ties to the lowest token are the first in that order.  (With 100 of
+          // 151936 tokens left, 8 stages of 8 children take 100 us, of 16 children
+          // 145; popping the best key below the last one took 219 and 601.)
+          int kk = p.kk, nbs = nb, left_s = left;
+          opaque(kk);  // (nothing of this is made ahead of the branch)
+          opaque(nbs);
+          asm volatile("" : "+v"(left_s));
+          const int want = min(max(kk, kHeadKeys), nbs);
+          float best = -INFINITY;
+#pragma unroll
+          for (int i = 0; i < kZPer; ++i) {
+            v[i] = v[i] >= -INFINITY ? v[i] : -INFINITY;
+            best = fmaxf(best, v[i]);
           }
+          const uint32_t ob = f32_ord(best);
+          uint32_t o4 = max(ob, perm<kXor1>(ob));
+          o4 = max(o4, perm<kXor2>(o4));
+          const uint32_t o8 = max(o4, perm<kHalfMirror>(o4));
+          uint32_t lo = least_group(o4, o8), hi = __builtin_amdgcn_readfirstlane(all_max<3>(o8));
+          auto at_least = [&](float t) __attribute__((always_inline)) {
+            int c = 0;
+#pragma unroll
+            for (int i = 0; i < kZPer; ++i) c += __popcll(__ballot(v[i] >= t));
+            return c;
+          };
+          int above = at_least(f32_unord(lo + 1));  // (past the largest value none are)
+          if (above > kCandCap) {
+#pragma unroll 1
+            while (lo < hi) {
+              const uint32_t mid = lo + (hi - lo + 1) / 2;
+              if (at_least(f32_unord(mid)) >= want)
+                lo = mid;
+              else
+                hi = mid - 1;
+            }
+            above = at_least(f32_unord(lo + 1));
+          }
+          const float T = f32_unord(lo);
+          int n = 0, ties = above;
+#pragma unroll
+          for (int i = 0; i < kZPer; ++i) {
+            const bool c = v[i] > T, e = v[i] == T && i * 64 < left_s;
+            const uint64_t mc = __ballot(c), me = __ballot(e);
+            if (mc | me) {
+              const uint64_t mm = c ? mc : me;
+              const int pos =
+                  (c ? n : ties) + (int)__builtin_amdgcn_mbcnt_hi(
+                                       (uint32_t)(mm >> 32),
+                                       __builtin_amdgcn_mbcnt_lo((uint32_t)mm, 0));
+              if (c || (e && pos < want)) cb[pos] = child_key(v[i], tb + i * step);
+              n += __popcll(mc);
+              ties += __popcll(me);
+            }
+          }
+          n = max(above, min(ties, want));
+          if (b > 0) {
+            if (lane < kk) cb[n + lane] = carried;
+            n += kk;
+          }
+          if (lane < 8) cb[n + lane] = 0;
+          __builtin_amdgcn_wave_barrier();
+          __atomic_signal_fence(__ATOMIC_SEQ_CST);
+          uint64_t keys[2];
+          int rank[2];
+          ranked(n, keys, rank);
+          lkey = in_order(keys, rank, max(kk, kHeadKeys));
         }
         if (last && (slow || nbatch > 1)) {
           if (lane < kRecWords) put(rec + lane * kSlicesMax, lane < kHeadKeys ? lkey | p.tag : sumw);
@@ -2142,7 +2215,8 @@ __device__ __forceinline__ void merge_block(const Plan& pl, FrontShared& fs, Mer
 #pragma unroll
       for (int i = 0; i < kHeadKeys; ++i)
         k[i] = live && (k[i] >> kTagBits) != 0 ? ((k[i] >> kTagBits) << kTagBits) | i : 0;
-      const float mv = live ? child_key_value(k[0]) : kNegBig;
+      // (as the slices' sums: relative to a finite value, also for -inf)
+      const float mv = live ? fmaxf(child_key_value(k[0]), -FLT_MAX) : -FLT_MAX;
       uint32_t hi = (uint32_t)(k[0] >> 30);
       hi = max(hi, perm<kXor1>(hi));
       if (gsh >= 2) hi = max(hi, perm<kXor2>(hi));
@@ -2187,15 +2261,34 @@ __device__ __forceinline__ void merge_block(const Plan& pl, FrontShared& fs, Mer
     }
     lds_barrier();
     if (!act || q != 0) continue;
-    const int n = ms.n[lrow];
+    int n = ms.n[lrow];
     if (lane == 0) ms.n[lrow] = 0;
     uint64_t* cand = ms.cand[lrow];
+    while (__builtin_expect(n > 64, 0)) {
+      // Many ties at the threshold (masked vocabularies with few tokens left):
+      // the k'-th largest of the lanes' bests is a higher one.  At most k' lanes
+      // have keys at or above it, 12 and then 3 each: twice at most.
+      uint64_t best = 0;
+      for (int e = lane; e < n; e += 64) best = cand[e] > best ? cand[e] : best;
+      uint64_t t = ~0ull;
+      for (int it = 0; it < kk; ++it) t = wave_max_u64(best < t ? best : 0);
+      int m = 0;
+      for (int e0 = 0; e0 < n; e0 += 64) {
+        const uint64_t key = e0 + lane < n ? cand[e0 + lane] : 0;
+        const uint64_t ge = __ballot(key >= t);
+        if (key >= t) cand[m + __popcll(ge & ((1ull << lane) - 1))] = key;
+        m += __popcll(ge);
+      }
+      n = m;
+      __builtin_amdgcn_wave_barrier();
+      __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    }
     if (lane < 8) cand[n + lane] = 0;  // (cand_rank reads eight at a time)
     __builtin_amdgcn_wave_barrier();
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
     // the lse over the waves' slices (lane i: wave i & 3)
     const float2 wm = (lane & 3) * 64 < G ? ms.wms[d & 1][lrow][lane & 3]
-                                          : make_float2(kNegBig, 0.0f);
+                                          : make_float2(-FLT_MAX, 0.0f);
     float M = fmaxf(wm.x, permf<kXor1>(wm.x));
     M = fmaxf(M, permf<kXor2>(M));
     float S = wm.y * exp2_raw((wm.x - M) * kLog2e);
@@ -2225,17 +2318,8 @@ __device__ __forceinline__ void merge_block(const Plan& pl, FrontShared& fs, Mer
       r0 = cand_rank(cand, n, key0);
       more = r0 < kk && (int)(key0 & kTagMask) == kHeadKeys - 1;
     }
-    for (int e = lane + 64; e < n; e += 64) {  // (many ties at the threshold)
-      const uint64_t key = cand[e];
-      more = more || ((int)(key & kTagMask) == kHeadKeys - 1 && cand_rank(cand, n, key) < kk);
-    }
     if (kk <= kHeadKeys || !__any(more)) {
       if (r0 < kk) publish(r0, key0);
-      for (int e = lane + 64; e < n; e += 64) {
-        const uint64_t key = cand[e];
-        const int rank = cand_rank(cand, n, key);
-        if (rank < kk) publish(rank, key);
-      }
       if (p.mode == 0 && d + 1 < p.B) {
         // the children's embedding rows into the memory-side cache: the
         // streaming workgroups read the chosen ones as soon as they have
@@ -2259,18 +2343,13 @@ __device__ __forceinline__ void merge_block(const Plan& pl, FrontShared& fs, Mer
     for (int i = 0; i < 16; ++i) lst[i] = 0;
     int nwin = 0;
     uint64_t mykey = 0;
-    for (int e0 = 0; e0 < n; e0 += 64) {
-      const int e = e0 + lane;
-      const uint64_t key = e < n ? cand[e] : 0;
-      const bool head = e < n && (key & kTagMask) == 0 && cand_rank(cand, n, key) < kk;
-      uint64_t b = __ballot(head);
-      while (b) {
-        const int src = __builtin_ctzll(b);
-        b &= b - 1;
-        const uint64_t kx = readlane_u64(key, src);
-        if (lane == nwin) mykey = kx;
-        ++nwin;
-      }
+    uint64_t heads = __ballot(r0 < kk && (key0 & kTagMask) == 0);
+    while (heads) {
+      const int src = __builtin_ctzll(heads);
+      heads &= heads - 1;
+      const uint64_t kx = readlane_u64(key0, src);
+      if (lane == nwin) mykey = kx;
+      ++nwin;
     }
     const int myslice = lane < nwin ? child_key_token(mykey) / kTile % G : 0;
     const uint64_t* src =

@@ -144,3 +144,69 @@ def test_rounds_repeat_bit_for_bit(k, R, dt):
             torch.cuda.synchronize()
             for n, t in ref.items():
                 assert torch.equal(out[n], t), f"draw {draw} run {i}: {n} differs"
+
+
+@pytest.mark.parametrize("low", [-np.inf, -np.finfo(np.float32).max, -1e30])
+@pytest.mark.parametrize("V,k,R,allowed,slices", [
+    (5000, 8, 1, 60, 0),      # most slices are masked whole
+    (5000, 3, 2, 40, 0),
+    (5000, 16, 1, 30, 0),     # two rows per wave
+    (5000, 8, 1, 3, 0),       # fewer unmasked tokens than children
+    (3000, 4, 1, 2500, 0),
+    (2600, 8, 1, 25, 2),      # two batches of logits per slice
+    (12, 8, 1, 5, 0),         # one tile
+])
+def test_masked_vocabulary(V, k, R, allowed, slices, low):
+    """Most base logits at one low value, as constrained decoding masks them: the
+    tree of the per-stage launches, and of the oracle where scores are finite."""
+    print(f"[edges] masked V={V} k={k} allowed={allowed} {low}", flush=True)
+    w = Workload("mask", V=V, B=4, N=40, k=k, r=32, R=R, dtype="f32", peak="none", seed=13)
+    inp = make_inputs(w)
+    rng = np.random.default_rng(13)
+    for q in range(R):
+        for d in range(w.B):
+            off = rng.permutation(V)[allowed:]
+            inp["L"][q, d, off] = np.float32(low)
+    out = {n: t.cpu().numpy() for n, t in _run(w, inp, slices).items()}
+    P.debug_set(force_multilaunch=True)
+    try:
+        b = P.TreeBuilder(w.V, w.B, w.N, w.k, w.r, w.R, P.F32, mask=True, trace=True)
+        ref = {n: t.cpu().numpy() for n, t in b.run(**P.device_inputs(inp)).items()}
+    finally:
+        P.debug_set()
+    for n, a in ref.items():
+        if a.dtype != np.float32:
+            np.testing.assert_array_equal(out[n], a, err_msg=n)
+        else:  # (a sum of two lowest values overflows in either order of adding)
+            np.testing.assert_allclose(out[n], a, rtol=1e-6, atol=C.SCORE_GUARD, err_msg=n)
+    assert not np.isnan(out["logprob"]).any()
+    if low == -1e30 and allowed >= k:
+        reps = C.compare_batch(out, inp, k, w.N, label=f"masked V{V}k{k}")
+        assert all(rep["exact"] or rep["identical"] for rep in reps), reps
+
+
+@pytest.mark.parametrize("k", [1, 8, 16])
+def test_two_levels_of_equal_logits(k):
+    """More than 64 equal logits above many equal ones: ties to the lowest tokens."""
+    print(f"[edges] two levels k={k}", flush=True)
+    w = Workload("levels", V=3 * 40 * 16, B=3, N=30, k=k, r=32, R=1, dtype="f32", peak="none",
+                 seed=14, sigma_L=0.0, sigma_W=0.0)
+    inp = make_inputs(w)
+    inp["L"][:, :, 500:1400] = np.float32(2.0)
+    inp["L"][:, 1, 700] = np.float32(3.0)
+    out = _run(w, inp, 3)
+    reps = C.compare_batch(out, inp, k, w.N, label=f"two levels k={k}")
+    assert all(rep["identical"] for rep in reps), reps
+
+
+def test_non_finite_logits_still_end():
+    """NaN and infinities among the base logits (outside the contract): the round
+    runs to its end at once, as the per-stage launches do."""
+    print("[edges] non-finite logits", flush=True)
+    w = Workload("nan", V=4000, B=3, N=20, k=8, r=32, R=1, dtype="f32", peak="uniform", seed=15)
+    for bad in (np.nan, np.inf, -np.inf):
+        for share in (1.0, 0.999, 0.01):
+            inp = make_inputs(w)
+            inp["L"][np.random.default_rng(1).random(inp["L"].shape) < share] = np.float32(bad)
+            out = _run(w, inp)
+            assert (out["count"] == w.N).all()

@@ -3753,37 +3753,48 @@ struct DeviceInfo {
   size_t lds_free[kRoundFns] = {};  // dynamic LDS each round kernel may use (0: does not run)
 };
 
-const DeviceInfo& device_info() {
-  static const DeviceInfo none;
+// Asks the runtime about device dev; whether every query succeeded.
+bool query_device(int dev, DeviceInfo& di) {
+  int cus = 0, khz = 0, lds = 0;
+  bool ok =
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
+      hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev) == hipSuccess &&
+      hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess;
+  di.ticks_per_s = (long long)(khz > 0 ? khz : 100000) * 1000;
+  di.cus = cus;
+  for (int i = 0; ok && i < kRoundFns; ++i) {
+    const void* fn = (const void*)kRoundFn[i];
+    hipFuncAttributes attr{};
+    int fit = 0;
+    ok = hipFuncGetAttributes(&attr, fn) == hipSuccess;
+    const int room = lds - (int)attr.sharedSizeBytes;
+    if (!ok || room <= 0) continue;
+    ok = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, room) == hipSuccess &&
+         hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit, fn, kRoundWaves * 64, room) ==
+             hipSuccess;
+    if (ok && fit > 0) di.lds_free[i] = room;
+  }
+  return ok;
+}
+
+// Only facts without a failed query are kept: after a failure this call takes
+// the per-stage launches and the next one asks again.
+DeviceInfo device_info() {
   static DeviceInfo cache[64];
-  static std::once_flag once[64];
+  static std::atomic<bool> known[64];
+  static std::mutex mutex;
   int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return none;
-  DeviceInfo& di = cache[dev];
-  std::call_once(once[dev], [&di, dev] {
-    int cus = 0, khz = 0, lds = 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-      cus = 0;
-    if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev) != hipSuccess) khz = 0;
-    if (hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
-      lds = 0;
-    di.ticks_per_s = (long long)(khz > 0 ? khz : 100000) * 1000;
-    di.cus = cus;
-    for (int i = 0; i < kRoundFns; ++i) {
-      const void* fn = (const void*)kRoundFn[i];
-      hipFuncAttributes attr{};
-      int fit = 0;
-      if (hipFuncGetAttributes(&attr, fn) != hipSuccess || lds <= (int)attr.sharedSizeBytes)
-        continue;
-      const int room = lds - (int)attr.sharedSizeBytes;
-      if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, room) ==
-              hipSuccess &&
-          hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit, fn, kRoundWaves * 64, room) ==
-              hipSuccess &&
-          fit > 0)
-        di.lds_free[i] = room;
-    }
-  });
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return DeviceInfo{};
+  if (known[dev].load(std::memory_order_acquire)) return cache[dev];
+  std::lock_guard<std::mutex> lock(mutex);
+  if (known[dev].load(std::memory_order_relaxed)) return cache[dev];
+  DeviceInfo di;
+  if (!query_device(dev, di)) {
+    (void)hipGetLastError();  // (it is not this call's: its launches report their own)
+    return DeviceInfo{};
+  }
+  cache[dev] = di;
+  known[dev].store(true, std::memory_order_release);
   return di;
 }
 
@@ -3798,11 +3809,12 @@ hipError_t launch_round(const Plan& p0, hipStream_t st) {
   const DebugConfig dbg = debug_config();
   const bool narrow = p0.R * p0.kk <= kNarrowRows && !dbg.force_multilaunch;
   Plan p = p0;
-  const DeviceInfo& di = device_info();
+  DeviceInfo di;
   RoundFn rfn = nullptr;
   int fit = 0;
   size_t smem = 0;
   if (narrow) {
+    di = device_info();
     // one mergers' workgroup per row (two rows with more than 8), one keeper
     // per request and a streaming slice on every remaining CU: every workgroup
     // is resident at once

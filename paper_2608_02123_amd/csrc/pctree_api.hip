@@ -470,13 +470,14 @@ pctree_status pctree_tree_attention(const pctree_attn_shape* shape, const void* 
     a.qblocks = plan.qblocks;
     a.nsplit = plan.nsplit;
     a.split_keys = plan.split_keys;
+    a.order = plan.order;
     a.scale_log2 = shape->scale * 1.4426950408889634f;
     const size_t rows = (size_t)a.R * a.N * a.Hq;
     a.part_o = plan.nsplit > 1 ? (float*)workspace : nullptr;
     a.part_ml = plan.nsplit > 1 ? (float*)workspace + (size_t)plan.nsplit * rows * shape->head_dim
                                 : nullptr;
     (void)hipGetLastError();
-    const hipError_t e = launch_attention(a, plan.blocks, shape->head_dim, (hipStream_t)stream);
+    const hipError_t e = launch_attention(a, plan, shape->head_dim, (hipStream_t)stream);
     return e == hipSuccess ? PCTREE_OK : PCTREE_ERR_HIP;
   } catch (...) {
     return PCTREE_ERR_HIP;

@@ -9,11 +9,16 @@
 
 namespace pctree {
 
+// The kernel of a layer (pctree_attention.hip describes them).
+enum AttnKernel { kAttnDirect16, kAttnDirect32, kAttnOneGroup, kAttnTwoGroups };
+
 // Work split of one call, a pure function of the shape and the CU count.
 struct AttnPlan {
+  AttnKernel kernel;
   int qblocks;      // 128-row query blocks per (request, key/value head)
   int nsplit;       // key-slot runs per query block (1: no merge pass)
   int split_keys;   // slots per run, a multiple of 64
+  int order;        // requests are taken longest first
   int blocks;       // workgroups of the attention kernel (XCD-grouped, padded)
   size_t ws_bytes;  // workspace of the merge pass (0 when nsplit == 1)
 };
@@ -29,12 +34,12 @@ struct AttnArgs {
   float* part_o;          // [nsplit][R][N][Hq][D] (split runs only)
   float* part_ml;         // [nsplit][R][N][Hq][2] (max of q.k, sum of weights)
   int R, N, Hq, Hkv, C, NW, g;
-  int qblocks, nsplit, split_keys;
+  int qblocks, nsplit, split_keys, order;
   float scale_log2;       // softmax scale times log2(e), > 0
 };
 
 AttnPlan plan_attention(int R, int N, int Hq, int Hkv, int D, int C, int cus);
 
-hipError_t launch_attention(AttnArgs a, int blocks, int D, hipStream_t stream);
+hipError_t launch_attention(const AttnArgs& a, const AttnPlan& plan, int D, hipStream_t stream);
 
 }  // namespace pctree

@@ -13,7 +13,9 @@
 // of it when there are too few workgroups to fill the chip).  Its eight waves
 // are two groups of four (32 rows each) that take the run's 64-slot chunks in
 // turn and join their results at the end, so that two waves share a SIMD and a
-// long request's chain of chunks is half as long.  K and V of a chunk go from
+// long request's chain of chunks is half as long.  Short runs, and layers of
+// many workgroups, have one group: no join, and two workgroups to a compute
+// unit (plan_attention).  K and V of a chunk go from
 // memory straight into LDS (no registers, no staging instructions), one chunk
 // ahead, both row-major with their 16-byte units permuted so that the fragment
 // reads touch all banks; V's fragments are read with the transposing LDS read.
@@ -31,7 +33,7 @@
 // kernel gives each of a workgroup's eight waves its own chunks for 16 or 32
 // rows, and joins them in LDS; longer caches are split over workgroups, whose
 // runs leave (max, sum, unnormalised output) per row in the workspace for a
-// merging kernel.
+// merging kernel.  plan_attention chooses.
 //
 // What bounds the first is instruction issue: staging through registers
 // (zeroing, transposing V by 16-bit stores) and the softmax took 460 vector
@@ -52,14 +54,12 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
-constexpr int kGroups = 2;         // slot groups of a workgroup, 4 waves each
-constexpr int kGroupThreads = 256;
-constexpr int kThreads = kGroups * kGroupThreads;
+constexpr int kGroupThreads = 256;  // a slot group: 4 waves
 constexpr int kColTiles = 2;       // 16-row MFMA column tiles per wave
 constexpr int kRowsPerWave = 16 * kColTiles;
 constexpr int kRowsPerBlock = 4 * kRowsPerWave;  // query rows of one workgroup
 constexpr int kChunk = 64;         // key slots per LDS stage (two 32-slot halves)
-constexpr int kMaxSplits = 32;     // slot runs merged by one merge thread
+constexpr int kMaxSplits = 32;     // slot runs of a layer at most
 constexpr int kXcds = 8;           // L2 domains the dispatcher deals workgroups over
 constexpr int kMergeThreads = 256;
 constexpr int kMergeBatch = 8;     // slot runs whose loads one merge thread issues together
@@ -160,8 +160,9 @@ __device__ __forceinline__ Work work_of(const AttnArgs& a, int qblocks, int nspl
   w.r = grp / nsplit / a.Hkv;
   // Longest requests first (up to 64 requests, one per lane): the workgroups
   // that start last, on the compute units that are free first, are then the
-  // shortest ones.
-  if (a.R > 1 && a.R <= 64 && w.ok) {
+  // shortest ones.  (Not where all start at once: the lengths come from memory,
+  // and the K and V loads wait for them.)
+  if (a.order && w.ok) {
     const int lane = threadIdx.x & 63;
     const int len = lane < a.R ? req_range(a, min(lane, a.R - 1)).end : -1;
     int rank = 0;
@@ -251,8 +252,8 @@ __device__ __forceinline__ uint32_t admitted(const AttnArgs& a, const ReqRange& 
   return ((uint32_t)(win >> (8 * grp)) & 0xffu) | ((uint32_t)(win >> (32 + 8 * grp)) & 0xffu) << 8;
 }
 
-template <int D>
-__global__ __launch_bounds__(kThreads) void attn_kernel(AttnArgs a) {
+template <int D, int G>
+__global__ __launch_bounds__(G * kGroupThreads) __attribute__((amdgpu_waves_per_eu(2))) void attn_kernel(AttnArgs a) {
   constexpr int KS = D / 32;   // contraction steps of S = K Q^T
   constexpr int DT = D / 16;   // 16-wide d tiles of O
   constexpr int UPR = D / 8;   // 16-byte units of a K or V row
@@ -260,10 +261,10 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnArgs a) {
   constexpr int TILE = kChunk * D;            // bf16 of a chunk's K (or V)
   constexpr int IPW = kChunk * UPR / 64 / 4;  // load instructions per wave, chunk and tensor
   // [group][buffer][K, V]
-  __shared__ __attribute__((aligned(16))) uint16_t sKV[kGroups][2][2][TILE];
-  __shared__ uint32_t sMask[kRowsPerBlock * (PCTREE_MAX_MASK_BUDGET / 32)];  // the nodes' mask rows
-  __shared__ float2 sML[kRowsPerBlock];  // the second group's row statistics
-  static_assert(kGroups == 2 && sizeof(sKV) >= kRowsPerBlock * D * sizeof(float),
+  __shared__ __attribute__((aligned(16))) uint16_t sKV[G][2][2][TILE];
+  extern __shared__ uint32_t sMask[];     // the nodes' mask rows (mask_bytes)
+  __shared__ float2 sML[kRowsPerBlock];  // (two groups) the second group's row statistics
+  static_assert(G == 1 || (G == 2 && sizeof(sKV) >= kRowsPerBlock * D * sizeof(float)),
                 "the second group's output fits the tiles");
 
   const Work wk = work_of(a, a.qblocks, a.nsplit);
@@ -329,7 +330,7 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnArgs a) {
   // the mask rows of the block's nodes (bit j of a row is tree node j, at slot
   // prefix + j)
   const uint32_t* mrow_g = a.mask + ((size_t)r * a.N + n0) * a.NW;
-  for (int i = threadIdx.x; i < nn * a.NW; i += kThreads) sMask[i] = mrow_g[i];
+  for (int i = threadIdx.x; i < nn * a.NW; i += G * kGroupThreads) sMask[i] = mrow_g[i];
 
   bool row_live[CT];
 #pragma unroll
@@ -357,12 +358,12 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnArgs a) {
 
   // (the step's base chunk is the first group's; the second may have one less)
   int buf = 0;
-  for (int cb = kbeg; cb < kend; cb += kGroups * kChunk, buf ^= 1) {
+  for (int cb = kbeg; cb < kend; cb += G * kChunk, buf ^= 1) {
     const int c0 = cb + group * kChunk;
     wait_loads();
     lds_barrier();  // the chunk is complete; the other buffer is no longer read
     if (c0 >= kend) break;  // (the last step: no barrier of the loop follows)
-    if (c0 + kGroups * kChunk < kend) fetch(c0 + kGroups * kChunk, buf ^ 1);
+    if (c0 + G * kChunk < kend) fetch(c0 + G * kChunk, buf ^ 1);
     const uint16_t* sK = sKV[group][buf][0];
     const uint16_t* sV = sKV[group][buf][1];
     // every slot of the chunk admitted for every live row: no masking (rows
@@ -429,29 +430,34 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnArgs a) {
   }
   // the second group's (max, sum, output) joins the first's, through the
   // tiles' place in LDS
-  lds_barrier();
   f32x4* sO = (f32x4*)sKV;
-  if (group == 1) {
+  if constexpr (G == 2) {
+    lds_barrier();
+    if (group == 1) {
 #pragma unroll
-    for (int c = 0; c < CT; ++c) {
+      for (int c = 0; c < CT; ++c) {
 #pragma unroll
-      for (int t = 0; t < DT; ++t) sO[((wave * CT + c) * DT + t) * 64 + lane] = o[c][t];
-      if (grp == 0) sML[wave * kRowsPerWave + 16 * c + col] = make_float2(m[c], l[c]);
+        for (int t = 0; t < DT; ++t) sO[((wave * CT + c) * DT + t) * 64 + lane] = o[c][t];
+        if (grp == 0) sML[wave * kRowsPerWave + 16 * c + col] = make_float2(m[c], l[c]);
+      }
     }
+    lds_barrier();
+    if (group == 1) return;
   }
-  lds_barrier();
-  if (group == 1) return;
 #pragma unroll
   for (int c = 0; c < CT; ++c) {
-    const float2 ml = sML[wave * kRowsPerWave + 16 * c + col];
-    const float mn = fmaxf(m[c], ml.x);
-    const float w0 = m[c] == mn ? 1.0f : exp2_hw((m[c] - mn) * a.scale_log2);
-    const float w1 = ml.x == mn ? 1.0f : exp2_hw((ml.x - mn) * a.scale_log2);
-    m[c] = mn;  // (both -inf, no admitted slot: weights 1 on zeros)
-    const float lc = l[c] * w0 + ml.y * w1;
+    float lc = l[c];
+    if constexpr (G == 2) {
+      const float2 ml = sML[wave * kRowsPerWave + 16 * c + col];
+      const float mn = fmaxf(m[c], ml.x);
+      const float w0 = m[c] == mn ? 1.0f : exp2_hw((m[c] - mn) * a.scale_log2);
+      const float w1 = ml.x == mn ? 1.0f : exp2_hw((ml.x - mn) * a.scale_log2);
+      m[c] = mn;  // (both -inf, no admitted slot: weights 1 on zeros)
+      lc = l[c] * w0 + ml.y * w1;
 #pragma unroll
-    for (int t = 0; t < DT; ++t)
-      o[c][t] = o[c][t] * w0 + sO[((wave * CT + c) * DT + t) * 64 + lane] * w1;
+      for (int t = 0; t < DT; ++t)
+        o[c][t] = o[c][t] * w0 + sO[((wave * CT + c) * DT + t) * 64 + lane] * w1;
+    }
     if (!row_in[c]) continue;
     const size_t qidx = ((size_t)r * a.N + node[c]) * a.Hq + hq[c];  // (request, node, head)
     if (a.nsplit == 1) {
@@ -722,56 +728,86 @@ AttnPlan plan_attention(int R, int N, int Hq, int Hkv, int D, int C, int cus) {
   const int per = (chunks + ns - 1) / ns;  // chunks per run
   p.split_keys = per * kChunk;
   p.nsplit = (chunks + per - 1) / per;
-  const long long groups = (long long)R * Hkv * p.nsplit;
-  p.blocks = (int)(((groups + kXcds - 1) / kXcds) * kXcds * p.qblocks);
   const size_t rows = (size_t)R * N * Hq;
   p.ws_bytes = p.nsplit > 1 ? (size_t)p.nsplit * rows * (D + 2) * sizeof(float) + 256 : 0;
+
+  // The kernel, by measurements over 1400 shapes (heads of 64 and 128, 16 to 128
+  // nodes, 1 to 8 requests, caches of 80 to 1628 slots); times in us, heads of
+  // 128 unless said otherwise.
+  //  * Direct: layers that would be split (fewer than 128 workgroups of 128
+  //    rows) while each wave has at most three chunks and all workgroups fit one
+  //    to a compute unit, with 16 rows each or else 32; with one chunk per wave
+  //    also at more.  Direct / split: up to 8 chunks 9.5 / 14, 9 to 16 10.4 /
+  //    15.5, 17 to 20 12.6 / 17.  Past 20 chunks runs of at most 4 chunks are
+  //    faster (17.8 / 16.4 at 96 workgroups of 16 rows, 24 chunks), but not with
+  //    heads of 64 (11 / 13.5).
+  //  * One group: runs of at most three chunks (10.2 / 10.6 at two, 11.7 / 12.3
+  //    at three, 14.1 / 13.6 at four: a second group then mostly adds the join).
+  //    Also with more workgroups than compute units, two of which fit a unit:
+  //    up to twice as many, the second group's shorter chains win from 12 to 18
+  //    chunks on (320 workgroups: 19.8 / 26.9 at 5 chunks, 28.2 / 31.9 at 12,
+  //    36.5 / 36.9 at 18, 58 / 50 at 34; heads of 64: 20.5 / 21.9 at 12, 26.5 /
+  //    25.2 at 18); beyond that one group always does (640: 49.8 / 57.8 at 18,
+  //    121 / 122 at 66).
+  const int q16 = (N * g + 15) / 16, q32 = (N * g + 31) / 32;
+  const long long heads = (long long)R * Hkv;
+  const bool short_runs = D == 128 && chunks > 20 && per <= 4;
+  if (p.nsplit > 1 && chunks <= kDirectChunks && !short_runs && heads * q16 <= cus)
+    p.kernel = kAttnDirect16;
+  else if (p.nsplit > 1 && chunks <= kDirectChunks && !short_runs &&
+           (heads * q32 <= cus || chunks <= kDirectWaves))
+    p.kernel = kAttnDirect32;
+  else
+    p.kernel = per <= 3 || (base > cus && chunks <= 12) || base > 2 * cus ? kAttnOneGroup
+                                                                       : kAttnTwoGroups;
+
+  // blocks: groups of workgroups that share K and V, padded to whole XCD rounds
+  const bool direct = p.kernel == kAttnDirect16 || p.kernel == kAttnDirect32;
+  const int qb = p.kernel == kAttnDirect16 ? q16 : (p.kernel == kAttnDirect32 ? q32 : p.qblocks);
+  const long long groups = heads * (direct ? 1 : p.nsplit);
+  p.blocks = (int)(((groups + kXcds - 1) / kXcds) * kXcds * qb);
+  // (an XCD has an eighth of the units and the padded blocks)
+  p.order = R > 1 && R <= 64 && p.blocks > cus;
   return p;
 }
 
 namespace {
 
-template <int D, int CT>
-hipError_t launch_direct(const AttnArgs& a, int qblocks, hipStream_t stream) {
-  const unsigned groups = (unsigned)((a.R * a.Hkv + kXcds - 1) / kXcds * kXcds);
-  attn_direct_kernel<D, CT><<<groups * qblocks, kDirectWaves * 64, 0, stream>>>(a, qblocks);
+// The mask rows of a workgroup's nodes: 128 rows touch at most 127 / g + 2 nodes.
+unsigned mask_bytes(const AttnArgs& a) {
+  const int nodes = (kRowsPerBlock - 1) / a.g + 2;
+  return (unsigned)((nodes < a.N ? nodes : a.N) * a.NW * sizeof(uint32_t));
+}
+
+template <int D>
+hipError_t launch(const AttnArgs& a, const AttnPlan& p, hipStream_t stream) {
+  const int rows = a.N * a.g;
+  switch (p.kernel) {
+    case kAttnDirect16:
+      attn_direct_kernel<D, 1><<<p.blocks, kDirectWaves * 64, 0, stream>>>(a, (rows + 15) / 16);
+      return hipGetLastError();
+    case kAttnDirect32:
+      attn_direct_kernel<D, 2><<<p.blocks, kDirectWaves * 64, 0, stream>>>(a, (rows + 31) / 32);
+      return hipGetLastError();
+    case kAttnOneGroup:
+      attn_kernel<D, 1><<<p.blocks, kGroupThreads, mask_bytes(a), stream>>>(a);
+      break;
+    case kAttnTwoGroups:
+      attn_kernel<D, 2><<<p.blocks, 2 * kGroupThreads, mask_bytes(a), stream>>>(a);
+      break;
+  }
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || a.nsplit == 1) return e;
+  const size_t out_rows = (size_t)a.R * a.N * a.Hq;
+  const int rpb = kMergeThreads / (D / 4);
+  attn_merge_kernel<D><<<(unsigned)((out_rows + rpb - 1) / rpb), kMergeThreads, 0, stream>>>(a);
   return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_attention(AttnArgs a, int blocks, int D, hipStream_t stream) {
-  // Layers that would be split (fewer than 128 workgroups of 128 rows) take
-  // the direct kernel while each wave has at most three chunks and all
-  // workgroups fit one to a compute unit, with 16 rows each or else 32; with
-  // one chunk per wave also at two per unit.  Against split runs, in us
-  // (heads of 128; N rows of nodes, 4 or 5 query heads to a key/value head):
-  //   one request, N 64:    C 256 7.0 / 13.7,  C 1536 17.6 / 19.1,  C 2048 22.1 / 19.9
-  //   one request, N 128:   C 256 9.2 / 16.6,  C 1536 20.3 / 25.9
-  //   two requests, N 128:  C 256 17.7 / 20.9, C 512 22.3 / 23.5,   C 1088 33.1 / 27.5
-  const int chunks = (a.C + kChunk - 1) / kChunk;
-  if (a.nsplit > 1 && chunks <= kDirectChunks) {
-    const int rows = a.N * a.g, q16 = (rows + 15) / 16, q32 = (rows + 31) / 32;
-    const long long heads = (long long)a.R * a.Hkv;
-    if (heads * q16 <= 256)
-      return D == 128 ? launch_direct<128, 1>(a, q16, stream) : launch_direct<64, 1>(a, q16, stream);
-    if (heads * q32 <= 256 || chunks <= kDirectWaves)
-      return D == 128 ? launch_direct<128, 2>(a, q32, stream) : launch_direct<64, 2>(a, q32, stream);
-  }
-  if (D == 128)
-    attn_kernel<128><<<blocks, kThreads, 0, stream>>>(a);
-  else
-    attn_kernel<64><<<blocks, kThreads, 0, stream>>>(a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || a.nsplit == 1) return e;
-  const size_t rows = (size_t)a.R * a.N * a.Hq;
-  const int rpb = kMergeThreads / (D / 4);
-  const unsigned mblocks = (unsigned)((rows + rpb - 1) / rpb);
-  if (D == 128)
-    attn_merge_kernel<128><<<mblocks, kMergeThreads, 0, stream>>>(a);
-  else
-    attn_merge_kernel<64><<<mblocks, kMergeThreads, 0, stream>>>(a);
-  return hipGetLastError();
+hipError_t launch_attention(const AttnArgs& a, const AttnPlan& plan, int D, hipStream_t stream) {
+  return D == 128 ? launch<128>(a, plan, stream) : launch<64>(a, plan, stream);
 }
 
 }  // namespace pctree

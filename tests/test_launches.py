@@ -78,3 +78,12 @@ def test_attention_kernels_over_the_range(tmp_path):
         assert r["kernels"][0][3] <= 24 * 1024  # (the mask rows, past the tiles)
         seen.add((want[0], len(want)))
     assert len(seen) == 2 * 6  # every kernel, split and not, for both head sizes
+
+
+def test_attention_edge_cases_take_the_kernels_they_name(tmp_path):
+    import test_gpu_attention_edges as E
+
+    shapes = [(len(c[5]), c[1], c[2], c[3], c[4], c[7]) for c in E.CASES]
+    for case, r in zip(E.CASES, _attention(tmp_path, shapes)):
+        assert _names(r)[0] == f"{case[8].format(D=case[4])}", case[0]
+        assert (len(r["kernels"]) == 2) == case[0].startswith("split runs"), case[0]

@@ -1747,6 +1747,9 @@ __device__ __forceinline__ void stream_block(const Plan& pl, FrontShared& fs, Ro
     }
 #pragma unroll
     for (int i = 0; i < RT; ++i) {
+      // (what a missing tile gives is not read; loading the last one in its place
+      // took 5 of the 21 us of a one-stage chain at V 1000, r 384)
+      if (wave + kRoundWaves * i >= nt0) break;
       const char* src = wsrc(wave + kRoundWaves * i, lane0);
 #pragma unroll
       for (int c = 0; c < NCMAX; ++c)

@@ -175,10 +175,14 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
+# (the current stream's handle without a stream object, where this torch has it)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream=None):
-    if stream is not None:
-        return stream.cuda_stream
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if stream is None and _raw_stream is not None:
+        return _raw_stream(torch.cuda.current_device())
+    return (stream if stream is not None else torch.cuda.current_stream()).cuda_stream
 
 
 def _dtype_code(t: torch.Tensor) -> int:

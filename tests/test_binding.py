@@ -88,3 +88,18 @@ def test_debug_set_validates_and_restores():
     P.debug_set(wait_ticks=0, force_multilaunch=True, round_slices=7, wide_unbounded=True)
     assert P.lib().pctree_debug_set(None) == P.OK
     P.debug_set()
+
+
+def test_current_stream_without_the_raw_handle(monkeypatch):
+    """The current stream is found with and without torch's raw-handle entry, and a
+    stream that is passed wins."""
+    class Stream:
+        cuda_stream = 0x1234
+
+    assert P._stream(Stream()) == 0x1234
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream())
+    monkeypatch.setattr(P, "_raw_stream", lambda dev: 0x77 if dev == 3 else 0)
+    assert P._stream() == 0x77
+    monkeypatch.setattr(P, "_raw_stream", None)
+    assert P._stream() == 0x1234

@@ -180,8 +180,9 @@ __device__ __forceinline__ float load_elem(const void* base, size_t i) {
 
 // Selection state of a round: the frontier (slot-indexed, kk per request) and
 // the running global top-N (sorted keys and pool ids, N per request).  It
-// lives in the workspace for the multi-launch form and in the selector
-// workgroup's LDS for the persistent form.
+// lives in the workspace for the multi-launch form (each selecting workgroup
+// works on a copy of its request's) and in a keeper workgroup's LDS for the
+// persistent form.
 // Entry i of request req sits at [(req - rbase) * kk + slot] (frontier) and
 // [(req - rbase) * N + i] (top-N): rbase 0 for state holding every request,
 // req for a copy of one request's.
@@ -698,9 +699,8 @@ __device__ __forceinline__ uint64_t* slice_record(const Plan& p, int stage, int 
 
 // Reduce the lanes' row states over the workgroup and publish the slice's
 // partial of every row.  Two reduction trees: the first carries only the
-// lanes' best four keys and the (max, sum) pairs and ends in the record, which
-// is all the keeper needs unless a row's record keys do not settle it; the
-// second then carries the full lists, which only that rare case reads.
+// lanes' best four keys and the (max, sum) pairs and ends in the record; the
+// second carries the full lists.
 // Rows live in lanes col, col+16, col+32, col+48 of every wave.
 template <int KMAX, int WAVES>
 __device__ __forceinline__ void publish_partial(const Plan& p, const HeadLane& h, int stage,
@@ -1341,12 +1341,19 @@ __device__ __forceinline__ void wait_vmcnt() {
 // W tiles are dealt to slices in turn (slice g owns tiles g, g + G, ...): the
 // likely tokens of a vocabulary have low ids, and a slice holding many of a
 // row's best tokens would make the merger read its full list.
+// Logits of up to 40 tiles of a slice fit LDS at once.  A vocabulary of more
+// (above about 158,000 tokens on 256 compute units; at 151,936 with more than 12
+// requests of one row, whose keepers and mergers leave fewer slices) takes
+// several batches, and then the lists and all records wait for the last one.
+// Rounds of 16 stages, 8 children, r 256, with one keeper / in this form: V 158,000
+// 234 / 155 us, V 202,048 283 / 243, V 262,144 367 / 307, V 2^20 (8 stages) 823 /
+// 766; chains of 12 and 13 requests 365 / 220 and 384 / 337.
 constexpr int kBatchTiles = 5;                        // tiles per wave of one logit batch
 constexpr int kZTiles = kBatchTiles * kRoundWaves;    // tiles whose logits LDS holds
 constexpr int kZPer = kZTiles * kTile / 64;           // logits of a row per lane
 constexpr int kZStride = kZTiles * kTile + 16;        // floats between rows (16 banks apart)
 
-// Tiles of a wave kept in registers for the whole round: at most 192 VGPRs of
+// Tiles of a wave kept in registers for the whole round: at most 144 VGPRs of
 // A fragments (the rest of the wave's 256 hold accumulators and the row
 // phase); the slice's other tiles are kept in LDS as far as they fit and are
 // read again every stage only past that.

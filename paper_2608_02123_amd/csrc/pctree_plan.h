@@ -79,7 +79,8 @@ struct Plan {
   uint64_t* part_key;// [stages][rows_max][kSlicesMax][kmax] per-slice candidate lists
   uint64_t* part_hd; // [stages][rows_max][kRecWords][kSlicesMax] slice records
   int* req_bad;      // [R] root token outside [0, V)
-  uint64_t* done_w;  // keepers of the persistent form that have their last stage
+  uint64_t* done_w;  // keepers of the persistent form that have their last stage (one word;
+                     // the rest of its room keeps the workspace the size it was)
   float* tau;        // [rows_max] wide stages: lower bound of each row's k'-th best logit
   int* probe_tok;    // [R][B][kProbe] wide stages: probe tokens of each request and depth
   void* probe_w;     // [R][B][kProbe][r] (dtype) their W rows (zero for a missing probe)
@@ -110,7 +111,8 @@ hipError_t launch_round(const Plan& p, hipStream_t stream);
 struct DebugConfig {
   long long wait_ticks = -1;  // < 0: 2 s of device wall clock per bounded wait
   int force_multilaunch = 0;  // nonzero: per-stage launches even for narrow rounds
-  int round_slices = 0;       // > 0: V-slices of the persistent round (else one per CU but one)
+  int round_slices = 0;       // > 0: V-slices of the persistent round at most (else one on
+                              // every CU that its mergers and keepers leave)
   int wide_unbounded = 0;     // nonzero: wide stages without their per-row bound
 };
 DebugConfig& debug_config();

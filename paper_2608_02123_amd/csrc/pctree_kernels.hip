@@ -3274,7 +3274,10 @@ __global__ __launch_bounds__(kWideWaves * 64) void head_thr_kernel(Plan p, int d
       const int row = wave + q * kWideWaves;  // token row of the super-tile
       const int t = min(t0 + 2 * s + row / kTile, t1 - 1);
       const int tok = min(t * kTile + (row & (kTile - 1)), p.V - 1);
-      const char* src = (const char*)p.Wt + (size_t)tok * p.r * ESZ + (size_t)min(lane, ru - 1) * 16;
+      // (32-bit factors, one multiply-add, here and for the head inputs: the address
+      // by 64-bit products took 8 of the round's 861 us at qwen14b_b16_r8)
+      const char* src = (const char*)p.Wt + min(lane, ru - 1) * 16 +
+                        (uint64_t)(uint32_t)tok * (uint32_t)(p.r * ESZ);
       if (lane < ru) load_lds16(src, slot_ptr(slot) + row * (ru + 1));
     }
     if constexpr (LL) {
@@ -3347,8 +3350,8 @@ __global__ __launch_bounds__(kWideWaves * 64) void head_thr_kernel(Plan p, int d
       const int i = wave + k * kWideWaves;  // row of the group
       const int gr = min(row0 + i, rows - 1);
       const int req = gr / P, slot = gr - req * P;
-      const char* src = (const char*)p.U + ((size_t)(req * p.kk + slot) * p.r) * ESZ +
-                        (size_t)min(lane, ru - 1) * 16;
+      const char* src = (const char*)p.U + min(lane, ru - 1) * 16 +
+                        (uint64_t)(uint32_t)(req * p.kk + slot) * (uint32_t)(p.r * ESZ);
       if (lane < ru) load_lds16(src, slot_ptr(i / (2 * kTile)) + (i % (2 * kTile)) * (ru + 1));
     }
     wait_vmcnt<0>();

@@ -14,8 +14,7 @@ namespace pctree {
 // between waves, a barrier.  M0 holds the LDS base; nothing else in the kernels
 // that use it keeps a value in M0 across it.  A load into LDS needs one wait
 // state after a scalar write of M0, which the compiler places around its own
-// instructions only: the s_nop (without it the load may use the M0 before; it
-// costs the wide head kernel 1.4 %, 849 -> 861 us per round of 8 requests).
+// instructions only: the s_nop (without it the load may use the M0 before).
 __device__ __forceinline__ uint32_t lds_base(const void* lds_dst) {
   return __builtin_amdgcn_readfirstlane(
       (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)lds_dst);
